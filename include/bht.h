@@ -211,7 +211,7 @@ bht_status bht_build_async_in(bht_table* t, const uint32_t* d_keys, const uint32
  * under stream capture, tight serving loops, harnesses that forbid
  * hipMalloc): as bht_build_async_in, but the partitioned path's workspace is
  * a fixed array inside the library (bht_build_noalloc_max_bytes() bytes,
- * 64 MiB: about 8 M pairs), one per GPU, held until the process ends, so
+ * about 64 MiB: about 8 M pairs), one per GPU, held until the process ends, so
  * the call allocates nothing.  Builds the default would give the concurrent
  * kernel need no workspace and take that kernel.  Finish with
  * bht_build_wait.  The table's device must be current.  CAPACITY when the
@@ -289,9 +289,10 @@ bht_status bht_get_probe_stats(const bht_table* t, uint64_t* build_probes, uint6
  * region's pairs in their first bucket in on-chip memory, writes the
  * buckets whole, lets each pair that met a full first bucket exchange
  * itself with a random resident there (Section III-A's eviction step, on
- * chip), and runs the concurrent cuckoo kernel only on the pairs evicted:
- * their chains continue concurrently, as in the concurrent build, and
- * since no bucket ever loses a pair the layout obeys the same invariants
+ * chip), and continues only the chains of the evicted pairs concurrently
+ * (a pair takes the first of its next two buckets with room before it
+ * evicts at the first of them); since no bucket ever loses a pair the
+ * layout obeys the same invariants
  * (every key in a candidate bucket, the early-exit property).  It allocates a
  * library-owned workspace of about 8-9 bytes per pair on first use (kept
  * until bht_destroy).  Iceberg tables (Section III-C) take the same path

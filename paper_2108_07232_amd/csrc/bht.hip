@@ -184,6 +184,44 @@ int grid_for(const void* kernel, uint64_t items, uint32_t fixed = 0, uint64_t it
   return (int)std::max<uint64_t>(1, grid);
 }
 
+// Work items per bin of an overflow phase over nbins bins run by `blocks`
+// blocks: as many (up to 8) as their waves cover, so that a small build's
+// evicted pairs spread over the device instead of one wave per bin.
+uint32_t overflow_parts(uint64_t blocks, uint64_t nbins) {
+  return (uint32_t)std::min<uint64_t>(
+      std::max<uint64_t>(blocks * (kBlock / 64) / std::max<uint64_t>(nbins, 1), 1), 8);
+}
+
+// Blocks of a cuckoo overflow phase of `items` work items: a wave each, at
+// most 4 blocks per CU.  A phase that fills the device is bound by the slot
+// atomics, and more lanes in flight only make them slower (2^27 pairs, LF
+// 0.9: 649, 590, 585, 592, 604 us at 2 to 6 blocks per CU).
+int overflow_grid(const void* kernel, uint64_t items) {
+  static std::mutex mu;
+  static std::map<int, int> known;
+  int dev = 0, cus = 0;
+  (void)hipGetDevice(&dev);
+  {
+    std::lock_guard<std::mutex> lock(mu);
+    auto it = known.find(dev);
+    if (it == known.end()) {
+      (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+      it = known.emplace(dev, std::max(1, cus)).first;
+    }
+    cus = it->second;
+  }
+  const uint64_t cap = std::min<uint64_t>(4ull * cus, resident_blocks(kernel, kBlock));
+  constexpr uint64_t kWaves = kBlock / 64;
+  return (int)std::max<uint64_t>(1, std::min<uint64_t>(cap, items / kWaves + (items % kWaves != 0)));
+}
+
+// Whether an overflow phase over nbins bins leaves waves without one, so
+// that latency bounds it and a pair's two next buckets are better looked at
+// at once.
+bool small_overflow(const void* kernel, uint64_t nbins) {
+  return nbins <= (uint64_t)overflow_grid(kernel, ~0ull) * (kBlock / 64);
+}
+
 Hash64 make_hash64(const bht_params& p, uint64_t m, uint32_t h) {
   Hash64 H;
   for (int i = 0; i < 4; ++i) {
@@ -438,6 +476,7 @@ constexpr uint64_t kIcebergPartMinKeys = 1ull << BHT_ICEBERG_PART_MIN_LOG2;
 struct PartKernels {
   const void* place;
   const void* overflow;
+  const void* overflow_both;   // the overflow insertion of small builds (cuckoo)
   bool iceberg;          // placement without eviction, iceberg overflow insertion
 };
 
@@ -450,7 +489,7 @@ bool part_kernels(const bht_table* t, uint32_t w, PartKernels* k) {
 #define BHT_ICASE(B_, B2_, W_)                                                     \
   if (b == B_ && b2 == B2_ && w == W_) {                                           \
     *k = {(const void*)bin_place_kernel<B_, false>,                                \
-          (const void*)iceberg_overflow_kernel<B_, B2_, W_>, true};                \
+          (const void*)iceberg_overflow_kernel<B_, B2_, W_>, nullptr, true};       \
     return true;                                                                   \
   }
     BHT_ICASE(16, 0, 8)
@@ -463,7 +502,9 @@ bool part_kernels(const bht_table* t, uint32_t w, PartKernels* k) {
   if (t->scheme != BHT_BCHT && t->scheme != BHT_CHT1) return false;
 #define BHT_PCASE(B_, W_)                                                          \
   if (b == B_ && w == W_) {                                                        \
-    *k = {(const void*)bin_place_kernel<B_>, (const void*)overflow_build_kernel<B_, W_>, false}; \
+    *k = {(const void*)bin_place_kernel<B_>,                                       \
+          (const void*)overflow_build_kernel<B_, false>,                           \
+          (const void*)overflow_build_kernel<B_, true>, false};                \
     return true;                                                                   \
   }
   BHT_PCASE(1, 1)
@@ -566,7 +607,7 @@ bool part_plan(const bht_table* t, uint64_t n, PartPlan* P) {
 // then values, in the slot array); keys/vals hold out_words words each.
 struct PartLayout {
   uint64_t hist1, hist2, total1, cursor1, seg_start, seg_len, chunk_first, chunk_seg, total2, cursor2,
-      bin_start, bin_len, ovf_len, head, keys, vals, bytes;
+      bin_start, bin_len, ovf_len, head, stats, keys, vals, bytes;
   uint64_t chunks1, chunks2, mid_words, out_words;
 };
 
@@ -598,7 +639,8 @@ PartLayout part_layout(const PartPlan& P, uint64_t n, uint32_t word_bytes = 4) {
   L.bin_start = take(P.nbins * 8ull);
   L.bin_len = take(P.nbins * 8ull);
   L.ovf_len = take(P.nbins * 4ull);
-  L.head = take(4);
+  L.head = take(kQueueHeads * kAtomicLine * 4);
+  L.stats = take(kStatLines * kAtomicLine * 4);
   L.keys = take(L.out_words * word_bytes);
   L.vals = take(L.out_words * word_bytes);
   L.bytes = off;
@@ -667,6 +709,7 @@ PartMeta part_meta(const PartLayout& L, char* w) {
   M.bin_len = reinterpret_cast<unsigned long long*>(w + L.bin_len);
   M.ovf_len = reinterpret_cast<uint32_t*>(w + L.ovf_len);
   M.head = reinterpret_cast<unsigned int*>(w + L.head);
+  M.stats = reinterpret_cast<unsigned long long*>(w + L.stats);
   return M;
 }
 
@@ -770,7 +813,8 @@ bht_status build64_partitioned(bht_table* t, const uint64_t* keys, const uint64_
   oa.g.rng_seed = (uint32_t)t->params.rng_seed;
   oa.M = M;
   oa.nbins = P.nbins;
-  const int og = grid_for((const void*)wide_overflow_kernel<8>, (uint64_t)P.nbins * 64,
+  oa.parts = overflow_parts(resident_blocks((const void*)wide_overflow_kernel<8>, kBlock), P.nbins);
+  const int og = grid_for((const void*)wide_overflow_kernel<8>, (uint64_t)P.nbins * oa.parts * 64,
                           t->grid_blocks);
   wide_overflow_kernel<8><<<og, kBlock, 0, st>>>(oa);
   HIP_TRY(hipGetLastError());
@@ -847,6 +891,7 @@ bht_status build32_partitioned(bht_table* t, const uint32_t* keys, const uint32_
     const uint64_t sec_buckets = t->params.iht_secondary_b ? t->params.iht_secondary_m : t->m;
     const uint64_t lanes = std::max<uint64_t>(sec_buckets / kIcebergOverflowSpread, 64);
     const int ig = grid_for(K.overflow, lanes, t->grid_blocks);
+    ia.parts = overflow_parts(ig, P.nbins);
     reinterpret_cast<void (*)(IcebergOverflowArgs)>(const_cast<void*>(K.overflow))
         <<<ig, kBlock, 0, st>>>(ia);
   } else {
@@ -862,8 +907,11 @@ bht_status build32_partitioned(bht_table* t, const uint32_t* keys, const uint32_
     oa.g.rng_seed = t->params.rng_seed;
     oa.M = M;
     oa.nbins = P.nbins;
-    const int og = grid_for(K.overflow, (uint64_t)P.nbins * 64, t->grid_blocks);
-    reinterpret_cast<void (*)(OverflowArgs)>(const_cast<void*>(K.overflow))
+    const void* kernel = small_overflow(K.overflow, P.nbins) ? K.overflow_both : K.overflow;
+    oa.parts = overflow_parts(overflow_grid(kernel, ~0ull), P.nbins);
+    const int og = t->grid_blocks ? (int)t->grid_blocks
+                                  : overflow_grid(kernel, (uint64_t)P.nbins * oa.parts);
+    reinterpret_cast<void (*)(OverflowArgs)>(const_cast<void*>(kernel))
         <<<og, kBlock, 0, st>>>(oa);
   }
   HIP_TRY(hipGetLastError());
@@ -1172,7 +1220,9 @@ bht_status bht_build_async_in(bht_table* t, const uint32_t* d_keys, const uint32
 // object, one copy per GPU, held until the process ends.  In host code the
 // array's name stands for a host-side shadow, never for device memory: its
 // device address comes from hipGetSymbolAddress, once per device.
-constexpr uint64_t kScratchBytes = 64ull << 20;
+// 64 MiB for pairs and counts and 64 KiB for the counters that are spread
+// over lines.
+constexpr uint64_t kScratchBytes = (64ull << 20) + (64ull << 10);
 static __device__ __align__(256) char scratch[kScratchBytes];
 
 namespace {
@@ -1664,10 +1714,12 @@ bht_status bht_batch_create(const bht_batch_entry* entries, uint32_t count, uint
   if (!bk) return fail(BHT_ERR_UNSUPPORTED, "no batched kernel for this bucket size and tile");
   const void* pk = nullptr;
   const void* ok = nullptr;
+  const void* ok_both = nullptr;
 #define BHT_BATCH_PCASE(B_, W_)                                   \
   if (t0->b == B_ && t0->tile == W_) {                            \
     pk = (const void*)batch_place_kernel<B_>;                     \
-    ok = (const void*)batch_overflow_kernel<B_, W_>;              \
+    ok = (const void*)batch_overflow_kernel<B_, false>;           \
+    ok_both = (const void*)batch_overflow_kernel<B_, true>;       \
   }
   BHT_BATCH_PCASE(8, 4)
   BHT_BATCH_PCASE(8, 8)
@@ -1769,7 +1821,7 @@ bht_status bht_batch_create(const bht_batch_entry* entries, uint32_t count, uint
       const uint64_t o_ovf = take(bins * 4), o_bt = take(bins * 4);
       const uint64_t o_parts = take(sizeof(BatchPart) * count);
       const uint64_t o_chunks = take(sizeof(BatchChunk) * std::max<size_t>(1, chunks.size()));
-      const uint64_t o_head = take(16);
+      const uint64_t o_head = take(kQueueHeads * kAtomicLine * 4);
       e = hipMalloc(&b->d_ws, off);
       if (e == hipSuccess) {
         char* w = static_cast<char*>(b->d_ws);
@@ -1798,7 +1850,8 @@ bht_status bht_batch_create(const bht_batch_entry* entries, uint32_t count, uint
           e = hipMemcpy(w + o_bt, bin_table.data(), 4 * bins, hipMemcpyHostToDevice);
         b->partitioned = e == hipSuccess;
         b->place_kernel = pk;
-        b->overflow_kernel = ok;
+        b->overflow_kernel = small_overflow(ok, bins) ? ok_both : ok;
+        pa.splits = overflow_parts(overflow_grid(b->overflow_kernel, ~0ull), bins);
       } else {
         b->d_ws = nullptr;          // not enough memory: the concurrent build serves
         e = hipSuccess;
@@ -1839,7 +1892,7 @@ bht_status batch_launch(bht_batch* b, hipStream_t st) {
     if (pa.n_chunks) batch_part_scatter_kernel<<<pa.n_chunks, kPassBlock, 0, st>>>(pa);
     reinterpret_cast<void (*)(BatchPartArgs)>(const_cast<void*>(b->place_kernel))
         <<<pa.nbins, kBinBlock, 0, st>>>(pa);
-    const int og = grid_for(b->overflow_kernel, (uint64_t)pa.nbins * 64);
+    const int og = overflow_grid(b->overflow_kernel, (uint64_t)pa.nbins * pa.splits);
     reinterpret_cast<void (*)(BatchPartArgs)>(const_cast<void*>(b->overflow_kernel))
         <<<og, kBlock, 0, st>>>(pa);
     HIP_TRY(hipGetLastError());

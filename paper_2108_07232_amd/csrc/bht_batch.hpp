@@ -159,6 +159,7 @@ struct BatchPartArgs {
   uint32_t count;                // tables
   uint32_t nbins;                // global bins
   uint32_t bin_shift;            // bins of 2^bin_shift buckets
+  uint32_t splits;               // overflow work items per bin
   uint32_t* hist;
   unsigned long long* total;     // per global bin
   unsigned long long* cursor;
@@ -174,7 +175,7 @@ struct BatchPartArgs {
 __global__ void batch_part_clear_kernel(BatchPartArgs a) {
   const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
   for (uint32_t j = i; j < a.nbins; j += gridDim.x * blockDim.x) a.total[j] = 0;
-  if (i == 0) *a.head = 0;
+  if (i < kQueueHeads) a.head[i * kAtomicLine] = 0;
 }
 
 __global__ __launch_bounds__(kPassBlock) void batch_part_hist_kernel(BatchPartArgs a) {
@@ -232,16 +233,14 @@ __global__ __launch_bounds__(kBinBlock) void batch_place_kernel(BatchPartArgs a)
   if (threadIdx.x == 0) a.ovf_len[g] = ovf;
 }
 
-// Pairs evicted during placement continue at their next bucket (cuckoo
-// insertion, Section III-A); waves take global bins from a queue.
-template <int B, int W>
+// Pairs evicted during placement continue at their next buckets (cuckoo
+// insertion, Section III-A).
+template <int B, bool BOTH>
 __global__ __launch_bounds__(kBlock) void batch_overflow_kernel(BatchPartArgs a) {
   const uint32_t salt = lane_salt();
-  for (;;) {
-    const uint32_t g = part_queue_pop(a.head);
-    if (g >= a.nbins) break;
-    const uint32_t len = a.ovf_len[g];
-    if (len == 0) continue;
+  for_bin_parts(a.head, a.nbins, a.splits, [&](uint32_t g, uint32_t part) {
+    const Range r = part_of(a.bin_start[g], a.ovf_len[g], part, a.splits);
+    if (r.cursor >= r.end) return;
     const uint32_t t = a.bin_table[g];
     const BatchTable& T = a.tables[t];
     BuildArgs32 b;
@@ -254,14 +253,11 @@ __global__ __launch_bounds__(kBlock) void batch_overflow_kernel(BatchPartArgs a)
     b.H = T.H;
     b.max_chain = T.max_chain;
     b.rng_seed = T.rng_seed;
-    Range r;
-    r.cursor = a.bin_start[g];
-    r.end = r.cursor + len;
     uint32_t probes = 0;
-    const uint32_t flags = cuckoo_build_range<B, W, false, true>(
+    const uint32_t flags = cuckoo_continue_range<B, BOTH>(
         b, r, T.rng_seed ^ salt ^ (g * 0x85EBCA6Bu), &probes);
     if (flags) atomicOr(a.status + t, flags);
-  }
+  });
 }
 
 // Small coalesced query launches pass their request descriptors as kernel

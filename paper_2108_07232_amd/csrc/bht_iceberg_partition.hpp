@@ -20,26 +20,19 @@ struct IcebergOverflowArgs {
   SchemeArgs32 g;                // keys / vals = the partitioned arrays
   PartMeta M;
   uint32_t nbins;
+  uint32_t parts;                // work items per bin
 };
 
-// Bucket reads of this phase are summed into status words 2-3.
 template <int B, int B2, int W>
 __global__ __launch_bounds__(kBlock) void iceberg_overflow_kernel(IcebergOverflowArgs a) {
-  uint32_t flags = 0, probes = 0;
-  for (;;) {
-    const uint32_t bin = part_queue_pop(a.M.head);
-    if (bin >= a.nbins) break;
-    const uint32_t len = a.M.ovf_len[bin];
-    if (len == 0) continue;
-    Range r;
-    r.cursor = a.M.bin_start[bin];
-    r.end = r.cursor + len;
-    flags |= iceberg_build_range<B, B2, W, true, true>(a.g, r, &probes);
-  }
+  uint32_t flags = 0, probes = 0, evicted = 0;
+  for_bin_parts(a.M.head, a.nbins, a.parts, [&](uint32_t bin, uint32_t part) {
+    const Range r = part_of(a.M.bin_start[bin], a.M.ovf_len[bin], part, a.parts);
+    evicted += (uint32_t)(r.end - r.cursor);
+    if (r.cursor < r.end) flags |= iceberg_build_range<B, B2, W, true, true>(a.g, r, &probes);
+  });
   if (flags) atomicOr(a.g.status, flags);
-  const uint32_t total = wave_sum(probes);
-  if (__lane_id() == 0 && total)
-    atomicAdd(reinterpret_cast<unsigned long long*>(a.g.status + 2), (unsigned long long)total);
+  add_overflow_stats(a.M.stats, a.g.status, evicted, probes);
 }
 
 }  // namespace bht

@@ -345,15 +345,12 @@ struct FindArgs32 {
   Hash32 H;
 };
 
-enum : uint32_t { kRead = 0, kWalk = 1, kEvict = 2 };
+enum : uint32_t { kRead = 0, kWalk = 1, kEvict = 2, kMove = 3 };
 
 // Bucketed cuckoo insertion (Section III-A, Section V-B) of the pairs in
 // range r by the calling wave.  Returns the status flags this lane raised;
-// *probes accumulates the lane's bucket reads when COUNT.  EVICTED: every
-// pair of the range was just evicted from its first bucket (one exchange
-// already made), so it continues at the next bucket of the cuckoo rule with
-// one exchange counted.
-template <int B, int W, bool COUNT, bool EVICTED = false>
+// *probes accumulates the lane's bucket reads when COUNT.
+template <int B, int W, bool COUNT>
 __device__ __forceinline__ uint32_t cuckoo_build_range(const BuildArgs32& g, Range r,
                                                        uint32_t rng, uint32_t* probes_out) {
   const uint32_t lane = __lane_id();
@@ -385,10 +382,6 @@ __device__ __forceinline__ uint32_t cuckoo_build_range(const BuildArgs32& g, Ran
         val = v_new;
         bucket = hash32(g.H, 0, key);
         chain = 0;
-        if (EVICTED) {
-          bucket = next_bucket(g.H, key, bucket);
-          chain = 1;
-        }
         phase = kRead;
       }
     }
@@ -435,6 +428,173 @@ __device__ __forceinline__ uint32_t cuckoo_build_range(const BuildArgs32& g, Ran
     }
   }
   if (COUNT) *probes_out += probes;
+  return flags;
+}
+
+// Where a key evicted from bucket `left` (first: from its first bucket) goes on: `at` is the next bucket of
+// the cuckoo rule (as next_bucket), `alt` the hash after it when there is one
+// (has_alt).  `full`: the key left the bucket of its last hash, so `at` is
+// its first one, which is known to be full (the key was evicted from it
+// before, and buckets never lose pairs).
+struct Choices {
+  uint32_t at, alt;
+  bool has_alt, full;
+};
+
+__device__ __forceinline__ Choices next_choices(const Hash32& H, uint32_t key, uint32_t left,
+                                                bool first) {
+  uint32_t hv[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) hv[i] = (i < (int)H.h) ? hash32(H, i, key) : 0u;
+  if (first) left = hv[0];
+  Choices c = {hv[0], 0u, false, false};
+#pragma unroll
+  for (int i = 3; i >= 0; --i) {
+    if (i < (int)H.h && hv[i] == left) {
+      const bool more = i + 1 < (int)H.h;
+      c.at = more ? hv[(i + 1) & 3] : hv[0];
+      c.alt = hv[(i + 2) & 3];
+      c.has_alt = i + 2 < (int)H.h;
+      c.full = !more;
+    }
+  }
+  return c;
+}
+
+// Occupied slots of one bucket, read by the calling lane alone.
+template <int B>
+__device__ __forceinline__ uint32_t lane_load(const uint64_t* bucket) {
+  if constexpr (B == 1) {
+    return (uint32_t)bucket[0] != kEmptyKey ? 1u : 0u;
+  } else {
+    u64x2 v[B / 2];
+#pragma unroll
+    for (int i = 0; i < B / 2; ++i) v[i] = reinterpret_cast<const u64x2*>(bucket)[i];
+    uint32_t load = 0;
+#pragma unroll
+    for (int i = 0; i < B / 2; ++i) {
+      load += (uint32_t)v[i].x != kEmptyKey ? 1u : 0u;
+      load += (uint32_t)v[i].y != kEmptyKey ? 1u : 0u;
+    }
+    return load;
+  }
+}
+
+// Cuckoo insertion of pairs just evicted from their first bucket (one
+// exchange made, chain 1 each): [r.cursor, r.end) of g.keys / g.vals, by the
+// calling wave.  A pair takes the first of its next two buckets, in hash
+// order, that has room; with both full it is exchanged at the first of them
+// (Section III-A), and the resident goes on the same way.  Looking at the
+// second bucket before evicting keeps the early-exit property (a pair sits
+// past a bucket only if that one is full) and the number of buckets a pair
+// sits beyond its first on average, but at LF 0.9 a chain goes on with
+// probability 0.22 instead of 0.47 per step, so a launch makes fewer slot
+// atomics and its slowest chain is half as long.
+// Every lane reads its own bucket: a small launch has few pairs per wave
+// left after the first steps and is bound by the instructions of the waves'
+// rounds, and 8 loads and 32 compares per bucket take a quarter of the
+// instructions of the tile-cooperative read (shuffles and ballots per tile
+// lane).
+// BOTH (launches that leave the device idle): the last slot of the second
+// bucket is read along with the first bucket, one latency less, and idle
+// lanes are refilled 16 or more at a time.  Otherwise (bound by the slot
+// atomics, where refilling late costs 5%) the second bucket is read only
+// when the first is full.
+// Measured at LF 0.9, with the counters of the phase spread over lines:
+// 2^20 pairs 50 -> 28 us (44 with tile reads), 2^27 pairs 819 -> 585 us
+// (about 9.8 M slot atomics at the 18 G/s of the whole table's region).
+template <int B, bool BOTH>
+__device__ __forceinline__ uint32_t cuckoo_continue_range(const BuildArgs32& g, Range r,
+                                                          uint32_t rng, uint32_t* probes_out) {
+  constexpr uint32_t kRefill = BOTH ? 16 : 1;
+  if (rng == 0) rng = 0x2545F491u;
+  Feed<uint32_t> fk, fv;
+  fk.init(g.keys, r, kEmptyKey);
+  fv.init(g.vals, r, 0u);
+  bool active = false, has_alt = false, fresh = false;
+  uint32_t key = 0, val = 0, bucket = 0, alt = 0, at = 0, chain = 0, slot = 0, phase = kRead;
+  uint32_t probes = 0, flags = 0;
+
+  for (;;) {
+    const uint64_t act = ballot(active);
+    if (fk.cursor < fk.end && 64u - (uint32_t)__popcll(act) >= kRefill) {
+      uint64_t idx;
+      const int64_t off = fk.claim(!active, &idx);
+      fv.claim(!active, &idx);
+      const uint32_t k_new = fk.value_at(off);
+      const uint32_t v_new = fv.value_at(off);
+      fk.advance(kEmptyKey);
+      fv.advance(0u);
+      if (off >= 0) {
+        if (k_new == kEmptyKey) {
+          flags |= kFlagSentinel;
+        } else {
+          active = fresh = true;
+          key = k_new;
+          val = v_new;
+          chain = 1;
+          phase = kMove;
+        }
+      }
+    } else if (act == 0) {
+      break;
+    }
+    if (active && phase == kMove) {
+      // evicted from its first bucket by the placement, or from bucket `at`
+      const Choices c = next_choices(g.H, key, at, fresh);
+      fresh = false;
+      bucket = at = c.at;
+      alt = c.alt;
+      has_alt = c.has_alt;
+      phase = c.full ? kEvict : kRead;
+    }
+    if (active && phase == kRead) {
+      uint64_t last = kEmptyPair;
+      if (BOTH && has_alt) last = g.slots[(uint64_t)alt * B + (B - 1)];
+      const uint32_t load = lane_load<B>(g.slots + (uint64_t)bucket * B);
+      ++probes;
+      if (load < (uint32_t)B) {
+        phase = kWalk;
+        slot = load;
+      } else if (!has_alt) {
+        phase = kEvict;
+      } else {
+        if (BOTH) ++probes;
+        has_alt = false;
+        bucket = alt;
+        if (BOTH && (uint32_t)last != kEmptyKey) phase = kEvict;   // full as well
+      }
+    }
+    const uint64_t pair = ((uint64_t)val << 32) | key;
+    if (active && phase == kWalk) {
+      const uint64_t old = cas64(g.slots + (uint64_t)bucket * B + slot, kEmptyPair, pair);
+      if (old == kEmptyPair) {
+        active = false;
+      } else if (++slot == (uint32_t)B) {
+        // the walk proved this bucket full
+        phase = has_alt ? kRead : kEvict;
+        has_alt = false;
+        bucket = alt;
+      }
+    } else if (active && phase == kEvict) {
+      if (chain >= g.max_chain) {
+        flags |= kFlagFailed;
+        active = false;
+      } else {
+        rng = xorshift32(rng);
+        const uint64_t old = xchg64(g.slots + (uint64_t)at * B + (rng % (uint32_t)B), pair);
+        if (old == kEmptyPair) {
+          active = false;
+        } else {
+          key = (uint32_t)old;
+          val = (uint32_t)(old >> 32);
+          ++chain;
+          phase = kMove;
+        }
+      }
+    }
+  }
+  *probes_out += probes;
   return flags;
 }
 

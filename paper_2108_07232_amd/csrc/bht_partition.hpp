@@ -129,8 +129,17 @@ struct PartMeta {
   unsigned long long* bin_start; // [nbins]
   unsigned long long* bin_len;   // [nbins]
   uint32_t* ovf_len;             // [nbins]
-  unsigned int* head;            // overflow queue head
+  unsigned int* head;            // overflow queue heads (kQueueHeads lines)
+  unsigned long long* stats;     // overflow counts (kStatLines lines)
 };
+
+// Atomics on one 128-byte line are performed one request after the other,
+// about 12 ns each (measured: 16,384 waves adding once, 200 us on one line,
+// 8 us spread over 64), so counters that every wave or block of a launch
+// touches are spread over lines.
+constexpr uint32_t kAtomicLine = 32;                   // 4-byte words per line
+constexpr uint32_t kQueueHeads = 16;
+constexpr uint32_t kStatLines = 64;
 
 // One radix pass over pairs of T keys and T values.  Level 1 reads the
 // caller's arrays as a single range of n pairs; level 2 reads the first
@@ -244,7 +253,8 @@ __global__ void part_clear_kernel(PartMeta M, uint32_t fan1, uint32_t levels,
   for (uint32_t j = i; j < fan1; j += stride) M.total1[j] = 0;
   if (levels == 2)
     for (uint32_t j = i; j < fan1 * kFan2; j += stride) M.total2[j] = 0;
-  if (i == 0) *M.head = 0;
+  if (i < kQueueHeads) M.head[i * kAtomicLine] = 0;
+  if (i < kStatLines * 2) M.stats[i / 2 * (kAtomicLine / 2) + i % 2] = 0;
   if (i < 8) status[i] = 0;
 }
 
@@ -984,16 +994,14 @@ __global__ __launch_bounds__(kBinBlock) void bin_place_kernel(BinArgs a) {
   const uint32_t ovf =
       place_bin<B, EVICT>(a.slots, a.keys, a.vals, a.P.H, R, first, nb, a.M.bin_start[bin],
                           a.M.bin_len[bin], a.max_chain, a.rng_seed, bin, a.cap, a.status);
-  if (threadIdx.x == 0) {
-    a.M.ovf_len[bin] = ovf;
-    if (ovf) atomicAdd(a.status + 1, ovf);       // evicted pairs of the build
-  }
+  if (threadIdx.x == 0) a.M.ovf_len[bin] = ovf;
 }
 
 struct OverflowArgs {
   BuildArgs32 g;                 // keys / vals = the partitioned arrays
   PartMeta M;
   uint32_t nbins;
+  uint32_t parts;                // work items per bin
 };
 
 __device__ __forceinline__ uint32_t part_queue_pop(unsigned int* head) {
@@ -1002,30 +1010,85 @@ __device__ __forceinline__ uint32_t part_queue_pop(unsigned int* head) {
   return (uint32_t)__builtin_amdgcn_readfirstlane(v);
 }
 
+// Calls f(bin, part) in every wave of the grid for its share of nbins * parts
+// work items: each wave starts with the item of its own number and, when
+// there are more items than waves, takes the following ones from the device
+// queue of its block (queue q of kQueueHeads holds the items nwaves + q +
+// kQueueHeads * i; a queue no block reads has its items taken by none, so
+// there are at most as many queues as blocks).
+template <typename F>
+__device__ __forceinline__ void for_bin_parts(unsigned int* heads, uint32_t nbins, uint32_t parts,
+                                              F f) {
+  const uint32_t wave =
+      __builtin_amdgcn_readfirstlane((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
+  const uint32_t nwaves = (gridDim.x * blockDim.x) >> 6;
+  const uint32_t items = nbins * parts;
+  const uint32_t queues = gridDim.x < kQueueHeads ? gridDim.x : kQueueHeads;
+  const uint32_t q = blockIdx.x % queues;
+  if (wave < items) f(wave / parts, wave % parts);
+  if (items <= nwaves) return;
+  for (;;) {
+    const uint32_t it = nwaves + q + queues * part_queue_pop(heads + q * kAtomicLine);
+    if (it >= items) break;
+    f(it / parts, it % parts);
+  }
+}
+
+// Adds the block's evicted pairs (wave-uniform counts) and bucket reads to
+// its stat line, and the line's sums to status words 1 (evicted) and 2-3
+// (bucket reads) when the block is the last of those that share the line.
+// Every thread of the block calls it, once.
+__device__ __forceinline__ void add_overflow_stats(unsigned long long* stats, uint32_t* status,
+                                                   uint32_t evicted, uint32_t probes) {
+  __shared__ uint32_t sum[2];
+  if (threadIdx.x < 2) sum[threadIdx.x] = 0;
+  __syncthreads();
+  const uint32_t p = wave_sum(probes);
+  if (__lane_id() == 0) {
+    if (evicted) atomicAdd(&sum[0], evicted);
+    if (p) atomicAdd(&sum[1], p);
+  }
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  const uint32_t l = blockIdx.x % kStatLines;
+  unsigned long long* line = stats + l * (kAtomicLine / 2);
+  const unsigned long long sharing = (gridDim.x - 1 - l) / kStatLines + 1;
+  // the evicted count is in place (its old value has come back) before the
+  // block is counted in the top 16 bits beside the bucket reads
+  const unsigned long long ev = atomicAdd(line, (unsigned long long)sum[0]);
+  if (ev == ~0ull) return;
+  const unsigned long long one = (1ull << 48) | sum[1];
+  const unsigned long long all = atomicAdd(line + 1, one) + one;
+  if (all >> 48 != sharing) return;
+  const unsigned long long total = atomicAdd(line, 0ull);
+  if (total) atomicAdd(status + 1, (uint32_t)total);
+  if (all << 16) atomicAdd(reinterpret_cast<unsigned long long*>(status + 2), all << 16 >> 16);
+}
+
+// Part p of `parts` of the len pairs at `start`.
+__device__ __forceinline__ Range part_of(uint64_t start, uint32_t len, uint32_t p,
+                                         uint32_t parts) {
+  Range r;
+  r.cursor = start + (uint64_t)len * p / parts;
+  r.end = start + (uint64_t)len * (p + 1) / parts;
+  return r;
+}
+
 // Cuckoo insertion (Section III-A) of the pairs evicted during placement,
-// each continuing at its next bucket with one exchange counted; waves take
-// bins from a queue.
-// The bucket reads of this phase are summed into status words 2-3 (one
-// atomic per wave).
-template <int B, int W>
+// each continuing at its next bucket with one exchange counted.
+template <int B, bool BOTH>
 __global__ __launch_bounds__(kBlock) void overflow_build_kernel(OverflowArgs a) {
   const uint32_t salt = lane_salt();
-  uint32_t flags = 0, probes = 0;
-  for (;;) {
-    const uint32_t bin = part_queue_pop(a.M.head);
-    if (bin >= a.nbins) break;
-    const uint32_t len = a.M.ovf_len[bin];
-    if (len == 0) continue;
-    Range r;
-    r.cursor = a.M.bin_start[bin];
-    r.end = r.cursor + len;
-    flags |= cuckoo_build_range<B, W, true, true>(
-        a.g, r, a.g.rng_seed ^ salt ^ (bin * 0x85EBCA6Bu), &probes);
-  }
+  uint32_t flags = 0, probes = 0, evicted = 0;
+  for_bin_parts(a.M.head, a.nbins, a.parts, [&](uint32_t bin, uint32_t part) {
+    const Range r = part_of(a.M.bin_start[bin], a.M.ovf_len[bin], part, a.parts);
+    evicted += (uint32_t)(r.end - r.cursor);
+    if (r.cursor < r.end)
+      flags |= cuckoo_continue_range<B, BOTH>(
+          a.g, r, a.g.rng_seed ^ salt ^ (bin * 0x85EBCA6Bu), &probes);
+  });
   if (flags) atomicOr(a.g.status, flags);
-  const uint32_t total = wave_sum(probes);
-  if (__lane_id() == 0 && total)
-    atomicAdd(reinterpret_cast<unsigned long long*>(a.g.status + 2), (unsigned long long)total);
+  add_overflow_stats(a.M.stats, a.g.status, evicted, probes);
 }
 
 }  // namespace bht

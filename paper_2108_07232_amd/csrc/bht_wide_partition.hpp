@@ -170,16 +170,14 @@ __global__ __launch_bounds__(kBinBlock) void bin_place64_kernel(BinArgs64 a) {
   const uint64_t first = (uint64_t)bin * R;
   const uint32_t nb = a.P.H64.m - first < (uint64_t)R ? (uint32_t)(a.P.H64.m - first) : R;
   const uint32_t ovf = place_bin64(a, R, first, nb, a.M.bin_start[bin], a.M.bin_len[bin], bin);
-  if (threadIdx.x == 0) {
-    a.M.ovf_len[bin] = ovf;
-    if (ovf) atomicAdd(a.status + 1, ovf);
-  }
+  if (threadIdx.x == 0) a.M.ovf_len[bin] = ovf;
 }
 
 struct WideOverflowArgs {
   WideBuildArgs g;               // keys / vals = the partitioned arrays
   PartMeta M;
   uint32_t nbins;
+  uint32_t parts;                // work items per bin
 };
 
 // Insertion of the pairs evicted during placement, bin by bin from a queue;
@@ -187,21 +185,16 @@ struct WideOverflowArgs {
 template <int W>
 __global__ __launch_bounds__(kBlock) void wide_overflow_kernel(WideOverflowArgs a) {
   const uint32_t salt = lane_salt();
-  uint32_t flags = 0, probes = 0;
-  for (;;) {
-    const uint32_t bin = part_queue_pop(a.M.head);
-    if (bin >= a.nbins) break;
-    const uint32_t len = a.M.ovf_len[bin];
-    if (len == 0) continue;
-    Range r;
-    r.cursor = a.M.bin_start[bin];
-    r.end = r.cursor + len;
-    flags |= wide_build_range<W, true>(a.g, r, a.g.rng_seed ^ salt ^ (bin * 0x85EBCA6Bu), &probes);
-  }
+  uint32_t flags = 0, probes = 0, evicted = 0;
+  for_bin_parts(a.M.head, a.nbins, a.parts, [&](uint32_t bin, uint32_t part) {
+    const Range r = part_of(a.M.bin_start[bin], a.M.ovf_len[bin], part, a.parts);
+    evicted += (uint32_t)(r.end - r.cursor);
+    if (r.cursor < r.end)
+      flags |=
+          wide_build_range<W, true>(a.g, r, a.g.rng_seed ^ salt ^ (bin * 0x85EBCA6Bu), &probes);
+  });
   if (flags) atomicOr(a.g.status, flags);
-  const uint32_t total = wave_sum(probes);
-  if (__lane_id() == 0 && total)
-    atomicAdd(reinterpret_cast<unsigned long long*>(a.g.status + 2), (unsigned long long)total);
+  add_overflow_stats(a.M.stats, a.g.status, evicted, probes);
 }
 
 }  // namespace bht

@@ -326,3 +326,29 @@ def test_partitioned_build_edge_sizes(scheme, b, n, cap):
     if st == B.BHT_OK:
         check_table(t, params, keys, vals, n_queries=max(2 * n, 64))
     t.close()
+
+
+@pytest.mark.parametrize("h,b,n,lf", [(2, 16, 70001, 0.8), (2, 4, 3000, 0.6), (4, 16, 70001, 0.95),
+                                      (4, 8, 1 << 18, 0.93), (3, 16, 300, 0.9), (3, 16, 1 << 19, 0.97)])
+def test_overflow_chains_by_hash_count(h, b, n, lf):
+    """Evicted pairs look at up to two buckets past the one they left before
+    they evict: with two hashes there is one, with four a third is left to the
+    next step.  The bin's evicted pairs are cut over several waves (small
+    builds) and lanes refill when a part holds more than 64.  The layout keeps
+    the early-exit property and the exact eviction count."""
+    B = bht()
+    keys, vals = workload(n, 81)
+    for s in range(10):
+        params = oracle.params_for("bcht", n, lf, 8100 + s, b=b, h=h)
+        t, st = build_partitioned(params, keys, vals)
+        if st == B.BHT_OK:
+            break
+        t.close()
+    else:
+        pytest.fail("no partitioned build succeeded")
+    check_table(t, params, keys, vals)
+    h0 = oracle.hash32_many(params.a[0], params.c[0], keys, params.m)
+    counts = np.bincount(h0.astype(np.int64), minlength=params.m)
+    part, evicted, probes = B.bht_build_stats(t.handle)
+    assert part and evicted == int(np.maximum(counts - b, 0).sum()) and probes >= evicted
+    t.close()
