@@ -354,6 +354,19 @@ struct KernelSet {
 
 constexpr uint32_t kDefaultSchedule = BHT_FIND_CHUNK;
 
+constexpr uint64_t kHeadBytes = kQueueHeads * kAtomicLine * 4;  // the heads of one queue
+
+// Queries per work item of a batch whose caller leaves the size open: about
+// 8 items per resident wave, in whole chunks of `chunk` queries, at most
+// 8,192.  Larger items leave waves idle at the end and small tables' items
+// without neighbours (256 tables, 12 M queries: 600 us at 8,192 per item,
+// 412, 320, 280, 247, 246 us at 1, 2, 4, 8, 16 items per wave).
+uint32_t find_item_size(const void* kernel, uint64_t queries, uint32_t chunk) {
+  const uint64_t waves = (uint64_t)resident_blocks(kernel, kBlock) * (kBlock / 64);
+  const uint64_t even = queries / (waves * 8) / chunk * chunk;
+  return (uint32_t)std::min<uint64_t>(std::max<uint64_t>(even, chunk), 8192);
+}
+
 template <int B, int W, bool C>
 KernelSet cuckoo_set(uint32_t schedule, uint32_t unroll) {
   const bool chunk = schedule == BHT_FIND_CHUNK || schedule == BHT_FIND_PARALLEL;
@@ -639,7 +652,7 @@ PartLayout part_layout(const PartPlan& P, uint64_t n, uint32_t word_bytes = 4) {
   L.bin_start = take(P.nbins * 8ull);
   L.bin_len = take(P.nbins * 8ull);
   L.ovf_len = take(P.nbins * 4ull);
-  L.head = take(kQueueHeads * kAtomicLine * 4);
+  L.head = take(kHeadBytes);
   L.stats = take(kStatLines * kAtomicLine * 4);
   L.keys = take(L.out_words * word_bytes);
   L.vals = take(L.out_words * word_bytes);
@@ -1675,7 +1688,8 @@ bht_status bht_batch_create(const bht_batch_entry* entries, uint32_t count, uint
   if (!out || (!entries && count)) return fail(BHT_ERR_INVALID_ARG, "null argument");
   *out = nullptr;
   if (count == 0) return fail(BHT_ERR_INVALID_ARG, "empty batch");
-  if (item_size == 0) item_size = 8192;
+  const bool open_size = item_size == 0;
+  if (open_size) item_size = 8192;
   if (item_size < 64) return fail(BHT_ERR_INVALID_ARG, "item_size must be at least 64");
   const bht_table* t0 = entries[0].table;
   if (!t0) return fail(BHT_ERR_INVALID_ARG, "null table");
@@ -1730,6 +1744,10 @@ bht_status bht_batch_create(const bht_batch_entry* entries, uint32_t count, uint
   BHT_BATCH_PCASE(32, 16)
 #undef BHT_BATCH_PCASE
 
+  uint64_t total_q = 0;
+  for (uint32_t i = 0; i < count; ++i) total_q += entries[i].n_queries;
+  const uint32_t find_size =
+      open_size ? find_item_size(fk, total_q, t0->unroll == 2 ? 128 : 64) : item_size;
   std::vector<BatchTable> tables(count);
   std::vector<BatchItem> fill, build, find;
   const uint64_t fill_words = 1ull << 16;
@@ -1753,9 +1771,11 @@ bht_status bht_batch_create(const bht_batch_entry* entries, uint32_t count, uint
       fill.push_back({i, 0, s, std::min<uint64_t>(fill_words, t->words - s)});
     for (uint64_t s = 0; s < e.n_keys; s += item_size)
       build.push_back({i, 0, s, std::min<uint64_t>(item_size, e.n_keys - s)});
-    for (uint64_t s = 0; s < e.n_queries; s += item_size)
-      find.push_back({i, 0, s, std::min<uint64_t>(item_size, e.n_queries - s)});
+    for (uint64_t s = 0; s < e.n_queries; s += find_size)
+      find.push_back({i, 0, s, std::min<uint64_t>(find_size, e.n_queries - s)});
   }
+  if (build.size() > 0xFFFFFFFFull || find.size() > 0xFFFFFFFFull)
+    return fail(BHT_ERR_CAPACITY, "more than 2^32 - 1 work items");
   bht_batch* b = new bht_batch();
   b->count = count;
   b->b = t0->b;
@@ -1821,7 +1841,7 @@ bht_status bht_batch_create(const bht_batch_entry* entries, uint32_t count, uint
       const uint64_t o_ovf = take(bins * 4), o_bt = take(bins * 4);
       const uint64_t o_parts = take(sizeof(BatchPart) * count);
       const uint64_t o_chunks = take(sizeof(BatchChunk) * std::max<size_t>(1, chunks.size()));
-      const uint64_t o_head = take(kQueueHeads * kAtomicLine * 4);
+      const uint64_t o_head = take(kHeadBytes);
       e = hipMalloc(&b->d_ws, off);
       if (e == hipSuccess) {
         char* w = static_cast<char*>(b->d_ws);
@@ -1861,7 +1881,7 @@ bht_status bht_batch_create(const bht_batch_entry* entries, uint32_t count, uint
   }
   if (e == hipSuccess) e = hipMalloc(&b->d_tables, sizeof(BatchTable) * count);
   if (e == hipSuccess) e = hipMalloc(&b->d_items, sizeof(BatchItem) * std::max<size_t>(1, all.size()));
-  if (e == hipSuccess) e = hipMalloc(&b->d_heads, 16);
+  if (e == hipSuccess) e = hipMalloc(&b->d_heads, 2 * kHeadBytes);
   if (e == hipSuccess) e = hipMalloc(&b->d_status, sizeof(uint32_t) * count);
   if (e == hipSuccess) e = hipHostMalloc(&b->h_status, sizeof(uint32_t) * count, hipHostMallocDefault);
   if (e == hipSuccess)
@@ -1902,19 +1922,19 @@ bht_status batch_launch(bht_batch* b, hipStream_t st) {
     HIP_TRY(hipGetLastError());
   }
   if (b->n_build && !b->partitioned) {
-    const int grid = grid_for(b->build_kernel, b->n_build * kBlock);
-    reinterpret_cast<void (*)(const BatchTable*, const BatchItem*, uint64_t, unsigned int*,
+    const int grid = grid_for(b->build_kernel, b->n_build * 64);
+    reinterpret_cast<void (*)(const BatchTable*, const BatchItem*, uint32_t, unsigned int*,
                               uint32_t*)>(const_cast<void*>(b->build_kernel))
-        <<<grid, kBlock, 0, st>>>(b->d_tables, b->d_items + b->n_fill, b->n_build, b->d_heads,
+        <<<grid, kBlock, 0, st>>>(b->d_tables, b->d_items + b->n_fill, (uint32_t)b->n_build, b->d_heads,
                                   b->d_status);
     HIP_TRY(hipGetLastError());
   }
   if (b->n_find) {
-    const int grid = grid_for(b->find_kernel, b->n_find * kBlock);
-    reinterpret_cast<void (*)(const BatchTable*, const BatchItem*, uint64_t, unsigned int*)>(
+    const int grid = grid_for(b->find_kernel, b->n_find * 64);
+    reinterpret_cast<void (*)(const BatchTable*, const BatchItem*, uint32_t, unsigned int*)>(
         const_cast<void*>(b->find_kernel))
-        <<<grid, kBlock, 0, st>>>(b->d_tables, b->d_items + b->n_fill + b->n_build, b->n_find,
-                                  b->d_heads + 1);
+        <<<grid, kBlock, 0, st>>>(b->d_tables, b->d_items + b->n_fill + b->n_build,
+                                  (uint32_t)b->n_find, b->d_heads + kHeadBytes / 4);
     HIP_TRY(hipGetLastError());
   }
   return BHT_OK;
@@ -2018,7 +2038,7 @@ bht_status bht_find_ctx_create(uint32_t max_requests, uint64_t max_items, bht_fi
   c->max_items = max_items;
   hipError_t e = hipMalloc(&c->d_tables, sizeof(BatchTable) * max_requests);
   if (e == hipSuccess) e = hipMalloc(&c->d_items, sizeof(BatchItem) * max_items);
-  if (e == hipSuccess) e = hipMalloc(&c->d_heads, 16);
+  if (e == hipSuccess) e = hipMalloc(&c->d_heads, 2 * kHeadBytes);
   if (e == hipSuccess)
     e = hipHostMalloc(&c->h_tables, sizeof(BatchTable) * max_requests, hipHostMallocDefault);
   if (e == hipSuccess)
@@ -2053,7 +2073,8 @@ bht_status bht_multi_find(bht_find_ctx* c, const bht_find_request* reqs, uint32_
       return fail(BHT_ERR_INVALID_ARG, "null data pointer in request");
     items += (r.n + item_size - 1) / item_size;
   }
-  if (items > c->max_items) return fail(BHT_ERR_CAPACITY, "more work items than the context holds");
+  if (items > c->max_items || items > 0xFFFFFFFFull)
+    return fail(BHT_ERR_CAPACITY, "more work items than the context holds");
   const void* fk = nullptr;
   const void* ik = nullptr;
 #define BHT_MF_CASE(B_, W_)                              \
@@ -2128,9 +2149,9 @@ bht_status bht_multi_find(bht_find_ctx* c, const bht_find_request* reqs, uint32_
   c->used = true;
   batch_reset_kernel<<<1, 64, 0, st>>>(c->d_heads, nullptr, 0);
   HIP_TRY(hipGetLastError());
-  const int grid = grid_for(fk, k * kBlock);
-  reinterpret_cast<void (*)(const BatchTable*, const BatchItem*, uint64_t, unsigned int*)>(
-      const_cast<void*>(fk))<<<grid, kBlock, 0, st>>>(c->d_tables, c->d_items, k, c->d_heads);
+  const int grid = grid_for(fk, k * 64);
+  reinterpret_cast<void (*)(const BatchTable*, const BatchItem*, uint32_t, unsigned int*)>(
+      const_cast<void*>(fk))<<<grid, kBlock, 0, st>>>(c->d_tables, c->d_items, (uint32_t)k, c->d_heads);
   HIP_TRY(hipGetLastError());
   return BHT_OK;
 }

@@ -38,12 +38,14 @@ struct BatchItem {
   uint64_t count;
 };
 
-// Clears the queue heads and every table's status word (no memset nodes, so
-// the sequence can be captured in a graph and replayed).
+// Clears the heads of the build's and the queries' queue and every table's
+// status word (no memset nodes, so the sequence can be captured in a graph
+// and replayed).
 __global__ void batch_reset_kernel(unsigned int* __restrict__ heads,
                                    uint32_t* __restrict__ status, uint32_t n_tables) {
   const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < 4) heads[i] = 0;
+  clear_heads(heads, i);
+  clear_heads(heads + kQueueHeads * kAtomicLine, i);
   for (uint32_t t = i; t < n_tables; t += gridDim.x * blockDim.x) status[t] = 0;
 }
 
@@ -60,22 +62,14 @@ __global__ __launch_bounds__(kBlock) void batch_fill_kernel(const BatchTable* __
   }
 }
 
-__device__ __forceinline__ uint64_t next_item(unsigned int* head) {
-  unsigned int v = 0;
-  if (__lane_id() == 0) v = atomicAdd(head, 1u);
-  return (uint64_t)__builtin_amdgcn_readfirstlane(v);
-}
-
 template <int B, int W>
 __global__ __launch_bounds__(kBlock) void batch_build_kernel(const BatchTable* __restrict__ tables,
                                                             const BatchItem* __restrict__ items,
-                                                            uint64_t n_items,
-                                                            unsigned int* __restrict__ head,
+                                                            uint32_t n_items,
+                                                            unsigned int* __restrict__ heads,
                                                             uint32_t* __restrict__ status) {
   const uint32_t salt = lane_salt();
-  for (;;) {
-    const uint64_t it = next_item(head);
-    if (it >= n_items) break;
+  for_items(heads, n_items, [&](uint32_t it) {
     const BatchItem item = items[it];
     const BatchTable& T = tables[item.table];
     BuildArgs32 g;
@@ -93,20 +87,17 @@ __global__ __launch_bounds__(kBlock) void batch_build_kernel(const BatchTable* _
     r.end = item.start + item.count;
     uint32_t probes = 0;
     const uint32_t flags =
-        cuckoo_build_range<B, W, false>(g, r, g.rng_seed ^ salt ^ (uint32_t)(it * 0x85EBCA6Bu),
-                                        &probes);
+        cuckoo_build_range<B, W, false>(g, r, g.rng_seed ^ salt ^ (it * 0x85EBCA6Bu), &probes);
     if (flags) atomicOr(g.status, flags);
-  }
+  });
 }
 
 template <int B, int W, int Q = 1>
 __global__ __launch_bounds__(kBlock) void batch_find_kernel(const BatchTable* __restrict__ tables,
                                                            const BatchItem* __restrict__ items,
-                                                           uint64_t n_items,
-                                                           unsigned int* __restrict__ head) {
-  for (;;) {
-    const uint64_t it = next_item(head);
-    if (it >= n_items) break;
+                                                           uint32_t n_items,
+                                                           unsigned int* __restrict__ heads) {
+  for_items(heads, n_items, [&](uint32_t it) {
     const BatchItem item = items[it];
     const BatchTable& T = tables[item.table];
     FindArgs32 g;
@@ -121,7 +112,7 @@ __global__ __launch_bounds__(kBlock) void batch_find_kernel(const BatchTable* __
     r.cursor = item.start;
     r.end = item.start + item.count;
     cuckoo_find_chunk_range<B, W, false, Q>(g, r);
-  }
+  });
 }
 
 // ---------------------------------------------- partitioned batched build
@@ -175,7 +166,7 @@ struct BatchPartArgs {
 __global__ void batch_part_clear_kernel(BatchPartArgs a) {
   const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
   for (uint32_t j = i; j < a.nbins; j += gridDim.x * blockDim.x) a.total[j] = 0;
-  if (i < kQueueHeads) a.head[i * kAtomicLine] = 0;
+  clear_heads(a.head, i);
 }
 
 __global__ __launch_bounds__(kPassBlock) void batch_part_hist_kernel(BatchPartArgs a) {
@@ -238,7 +229,8 @@ __global__ __launch_bounds__(kBinBlock) void batch_place_kernel(BatchPartArgs a)
 template <int B, bool BOTH>
 __global__ __launch_bounds__(kBlock) void batch_overflow_kernel(BatchPartArgs a) {
   const uint32_t salt = lane_salt();
-  for_bin_parts(a.head, a.nbins, a.splits, [&](uint32_t g, uint32_t part) {
+  for_items(a.head, a.nbins * a.splits, [&](uint32_t it) {
+    const uint32_t g = it / a.splits, part = it % a.splits;
     const Range r = part_of(a.bin_start[g], a.ovf_len[g], part, a.splits);
     if (r.cursor >= r.end) return;
     const uint32_t t = a.bin_table[g];

@@ -141,6 +141,39 @@ constexpr uint32_t kAtomicLine = 32;                   // 4-byte words per line
 constexpr uint32_t kQueueHeads = 16;
 constexpr uint32_t kStatLines = 64;
 
+__device__ __forceinline__ uint32_t queue_pop(unsigned int* head) {
+  unsigned int v = 0;
+  if (__lane_id() == 0) v = atomicAdd(head, 1u);
+  return (uint32_t)__builtin_amdgcn_readfirstlane(v);
+}
+
+// Clears the kQueueHeads heads of one queue (i = the calling thread of at
+// least kQueueHeads).
+__device__ __forceinline__ void clear_heads(unsigned int* heads, uint32_t i) {
+  if (i < kQueueHeads) heads[i * kAtomicLine] = 0;
+}
+
+// Calls f(item) in every wave of the grid for its share of `items` work
+// items: each wave starts with the item of its own number and, when there
+// are more items than waves, takes the following ones from the head of its
+// block (head q of `queues` hands out the items nwaves + q + queues * i; at
+// most as many heads as blocks, so each is read by some block).
+template <typename F>
+__device__ __forceinline__ void for_items(unsigned int* heads, uint32_t items, F f) {
+  const uint32_t wave =
+      __builtin_amdgcn_readfirstlane((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
+  const uint32_t nwaves = (gridDim.x * blockDim.x) >> 6;
+  const uint32_t queues = gridDim.x < kQueueHeads ? gridDim.x : kQueueHeads;
+  const uint32_t q = blockIdx.x % queues;
+  if (wave < items) f(wave);
+  if (items <= nwaves) return;
+  for (;;) {
+    const uint32_t it = nwaves + q + queues * queue_pop(heads + q * kAtomicLine);
+    if (it >= items) break;
+    f(it);
+  }
+}
+
 // One radix pass over pairs of T keys and T values.  Level 1 reads the
 // caller's arrays as a single range of n pairs; level 2 reads the first
 // pass's output as fan1 ranges (seg_*).
@@ -253,7 +286,7 @@ __global__ void part_clear_kernel(PartMeta M, uint32_t fan1, uint32_t levels,
   for (uint32_t j = i; j < fan1; j += stride) M.total1[j] = 0;
   if (levels == 2)
     for (uint32_t j = i; j < fan1 * kFan2; j += stride) M.total2[j] = 0;
-  if (i < kQueueHeads) M.head[i * kAtomicLine] = 0;
+  clear_heads(M.head, i);
   if (i < kStatLines * 2) M.stats[i / 2 * (kAtomicLine / 2) + i % 2] = 0;
   if (i < 8) status[i] = 0;
 }
@@ -1004,36 +1037,6 @@ struct OverflowArgs {
   uint32_t parts;                // work items per bin
 };
 
-__device__ __forceinline__ uint32_t part_queue_pop(unsigned int* head) {
-  unsigned int v = 0;
-  if (__lane_id() == 0) v = atomicAdd(head, 1u);
-  return (uint32_t)__builtin_amdgcn_readfirstlane(v);
-}
-
-// Calls f(bin, part) in every wave of the grid for its share of nbins * parts
-// work items: each wave starts with the item of its own number and, when
-// there are more items than waves, takes the following ones from the device
-// queue of its block (queue q of kQueueHeads holds the items nwaves + q +
-// kQueueHeads * i; a queue no block reads has its items taken by none, so
-// there are at most as many queues as blocks).
-template <typename F>
-__device__ __forceinline__ void for_bin_parts(unsigned int* heads, uint32_t nbins, uint32_t parts,
-                                              F f) {
-  const uint32_t wave =
-      __builtin_amdgcn_readfirstlane((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
-  const uint32_t nwaves = (gridDim.x * blockDim.x) >> 6;
-  const uint32_t items = nbins * parts;
-  const uint32_t queues = gridDim.x < kQueueHeads ? gridDim.x : kQueueHeads;
-  const uint32_t q = blockIdx.x % queues;
-  if (wave < items) f(wave / parts, wave % parts);
-  if (items <= nwaves) return;
-  for (;;) {
-    const uint32_t it = nwaves + q + queues * part_queue_pop(heads + q * kAtomicLine);
-    if (it >= items) break;
-    f(it / parts, it % parts);
-  }
-}
-
 // Adds the block's evicted pairs (wave-uniform counts) and bucket reads to
 // its stat line, and the line's sums to status words 1 (evicted) and 2-3
 // (bucket reads) when the block is the last of those that share the line.
@@ -1080,7 +1083,8 @@ template <int B, bool BOTH>
 __global__ __launch_bounds__(kBlock) void overflow_build_kernel(OverflowArgs a) {
   const uint32_t salt = lane_salt();
   uint32_t flags = 0, probes = 0, evicted = 0;
-  for_bin_parts(a.M.head, a.nbins, a.parts, [&](uint32_t bin, uint32_t part) {
+  for_items(a.M.head, a.nbins * a.parts, [&](uint32_t it) {
+    const uint32_t bin = it / a.parts, part = it % a.parts;
     const Range r = part_of(a.M.bin_start[bin], a.M.ovf_len[bin], part, a.parts);
     evicted += (uint32_t)(r.end - r.cursor);
     if (r.cursor < r.end)

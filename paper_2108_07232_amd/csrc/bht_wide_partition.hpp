@@ -186,7 +186,8 @@ template <int W>
 __global__ __launch_bounds__(kBlock) void wide_overflow_kernel(WideOverflowArgs a) {
   const uint32_t salt = lane_salt();
   uint32_t flags = 0, probes = 0, evicted = 0;
-  for_bin_parts(a.M.head, a.nbins, a.parts, [&](uint32_t bin, uint32_t part) {
+  for_items(a.M.head, a.nbins * a.parts, [&](uint32_t it) {
+    const uint32_t bin = it / a.parts, part = it % a.parts;
     const Range r = part_of(a.M.bin_start[bin], a.M.ovf_len[bin], part, a.parts);
     evicted += (uint32_t)(r.end - r.cursor);
     if (r.cursor < r.end)

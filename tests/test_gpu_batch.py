@@ -207,3 +207,30 @@ def test_batch_build_find_one_call():
         assert code == 0, msg
     for d in tabs:
         d["table"].close()
+
+
+@pytest.mark.parametrize("sizes,unroll", [
+    ([1], 2),                                  # one query, one item
+    ([127, 128, 129, 1, 64, 257], 1),          # around one chunk per item
+    ([700001, 3, 500003, 130000], 2),          # more items than resident waves, ragged ends
+])
+def test_batch_default_item_size(sizes, unroll):
+    """The size of the query items left open: it follows the number of queries
+    (whole chunks, several items per resident wave), and every query of every
+    table is answered, also when waves take further items from the queues."""
+    import torch
+    import paper_2108_07232_amd as bht
+    tabs = make_tables(len(sizes), 0, 0, 31, tile=4, unroll=unroll, sizes=sizes, lf=0.85)
+    entries = [(d["table"].handle, d["dk"], d["dv"], d["dq"], d["ov"], d["of"]) for d in tabs]
+    batch = bht.bht_batch_create(entries)
+    for _ in range(2):
+        for d in tabs:
+            d["ov"].fill_(123)
+            d["of"].fill_(5)
+        bht.bht_batch_run(batch)
+        rc, sts = bht.bht_batch_wait(batch, len(tabs))
+        assert rc == bht.BHT_OK, sts
+        check_outputs(tabs, sts)
+    bht.bht_batch_destroy(batch)
+    for d in tabs:
+        d["table"].close()
