@@ -299,9 +299,12 @@ bht_status bht_get_probe_stats(const bht_table* t, uint64_t* build_probes, uint6
  * with primaries filled on chip up to iht_threshold pairs and the rest
  * inserted at their secondary choices afterwards, concurrently (a pair
  * reaches the secondary level only once its primary holds iht_threshold
- * pairs, as the threshold rule requires).  BHT_BUILD_AUTO partitions builds of at least 2^18 pairs (2^26
- * for two-level iceberg tables, never one-level ones) into tables whose
- * memory the library owns (bht_create).
+ * pairs, as the threshold rule requires).  BHT_BUILD_AUTO partitions builds of at least 2^15 pairs
+ * (2^17 with fewer than 8 slots per bucket, 2^18
+ * for two-level iceberg and 64-bit tables, never one-level iceberg ones) into
+ * tables whose memory the library owns (bht_create); below 2^18 pairs only
+ * where the workspace is allocated or can be (not while the stream is
+ * captured).
  * iht_early_exit (iceberg tables only, else UNSUPPORTED): 1 makes a find
  * stop after a miss in a primary bucket that holds fewer than
  * iht_threshold keys, which proves absence because a key goes to a

@@ -473,8 +473,16 @@ Hash32 secondary_hash(const bht_table* t) {
 // ------------------------------------------------- partitioned build
 
 // Smallest build that takes the partitioned path by default: below it the
-// fixed cost of its eight launches outweighs the saved atomics.
-constexpr uint64_t kPartMinKeys = 1ull << 18;
+// fixed cost of its six launches outweighs the saved atomics (concurrent
+// against partitioned build at LF 0.9, us: 25,000 pairs 51.6 and 51.0,
+// 32,768 52 and 51, 50,000 58 and 42, 100,003 73 and 43, 200,000 111 and 48).
+// Builds below kPartWorkspaceKeys take it only where their workspace is at
+// hand or can be allocated, so that what builds without one (a captured
+// stream, a full device, the no-allocation entry point) still does.
+// Buckets of 1 or 4 slots cross later (4 slots, LF 0.8: 100,003 pairs 48 and
+// 51 us, 200,000 63 and 53): few pairs contend for a bucket's first slot.
+uint64_t part_min_keys(uint32_t b) { return b >= 8 ? 1ull << 15 : 1ull << 17; }
+constexpr uint64_t kPartWorkspaceKeys = 1ull << 18;
 // The same for two-level iceberg tables (at LF 0.85 the partitioned build
 // is 1.7-2.2x the concurrent one from 2^18 to 2^26 pairs, every build of
 // 12 succeeding on both).  One-level iceberg tables take the partitioned
@@ -488,6 +496,8 @@ constexpr uint64_t kIcebergPartMinKeys = 1ull << BHT_ICEBERG_PART_MIN_LOG2;
 
 struct PartKernels {
   const void* place;
+  const void* place_mid;       // bins of at most 2 * kSmallBinSlots slots
+  const void* place_small;     // bins of at most kSmallBinSlots slots
   const void* overflow;
   const void* overflow_both;   // the overflow insertion of small builds (cuckoo)
   bool iceberg;          // placement without eviction, iceberg overflow insertion
@@ -501,7 +511,9 @@ bool part_kernels(const bht_table* t, uint32_t w, PartKernels* k) {
     const uint32_t b2 = t->params.iht_secondary_b;
 #define BHT_ICASE(B_, B2_, W_)                                                     \
   if (b == B_ && b2 == B2_ && w == W_) {                                           \
-    *k = {(const void*)bin_place_kernel<B_, false>,                                \
+    *k = {(const void*)bin_place_kernel<B_, false, bin_slots<B_>()>,               \
+          (const void*)bin_place_kernel<B_, false, 2 * kSmallBinSlots>,            \
+          (const void*)bin_place_kernel<B_, false, kSmallBinSlots>,                \
           (const void*)iceberg_overflow_kernel<B_, B2_, W_>, nullptr, true};       \
     return true;                                                                   \
   }
@@ -515,7 +527,9 @@ bool part_kernels(const bht_table* t, uint32_t w, PartKernels* k) {
   if (t->scheme != BHT_BCHT && t->scheme != BHT_CHT1) return false;
 #define BHT_PCASE(B_, W_)                                                          \
   if (b == B_ && w == W_) {                                                        \
-    *k = {(const void*)bin_place_kernel<B_>,                                       \
+    *k = {(const void*)bin_place_kernel<B_, true, bin_slots<B_>()>,                \
+          (const void*)bin_place_kernel<B_, true, 2 * kSmallBinSlots>,             \
+          (const void*)bin_place_kernel<B_, true, kSmallBinSlots>,                 \
           (const void*)overflow_build_kernel<B_, false>,                           \
           (const void*)overflow_build_kernel<B_, true>, false};                \
     return true;                                                                   \
@@ -612,6 +626,15 @@ bool part_plan(const bht_table* t, uint64_t n, PartPlan* P) {
   }
   if (P->levels == 2 && !P->chunks2_cap)
     P->chunks2_cap = (uint32_t)second_pass_chunk_cap(n / P->chunk + P->fan1);
+  // Fewer than 64 chunks of 16 K pairs: sub-tiles of 4 K, so that a small
+  // build's passes run on more CUs (100,003 pairs, whole build: 48 against
+  // 52 us; no gain from 64 chunks on, where the partial lines written by
+  // more blocks outweigh it).
+  constexpr uint64_t kSmallSub = 4 * kPassBlock, kSmallChunks = 64;
+  if (P->levels == 1 && !P->lines1 && n < kSmallChunks * kPartSub) {
+    P->small_chunks = 1;
+    P->chunk = (uint32_t)(kSmallSub * ((n + kSmallChunks * kSmallSub - 1) / (kSmallChunks * kSmallSub)));
+  }
   return true;
 }
 
@@ -678,7 +701,32 @@ bool use_partitioned(const bht_table* t, uint64_t n, bool counting) {
   if (!t->owns_memory) return false;
   if (t->scheme == BHT_IHT)
     return t->params.iht_secondary_b != 0 && n >= kIcebergPartMinKeys;
-  return n >= kPartMinKeys;
+  return n >= kPartWorkspaceKeys;
+}
+
+bht_status part_workspace(bht_table* t, const PartLayout& L, hipStream_t st, void* ws,
+                          uint64_t ws_bytes, char** w);
+
+// Whether a cuckoo build below kPartWorkspaceKeys takes the partitioned path.
+bool use_small_partitioned(bht_table* t, uint64_t n, bool counting, hipStream_t st) {
+  if (counting || n < part_min_keys(t->b) || n >= kPartWorkspaceKeys) return false;
+  if ((t->scheme != BHT_BCHT && t->scheme != BHT_CHT1) || t->key_bits != 32) return false;
+  if (t->build_mode != BHT_BUILD_AUTO || !t->owns_memory) return false;
+  PartPlan P;
+  if (!part_plan(t, n, &P)) return false;
+  const PartLayout L = part_layout(P, n);
+  if (t->part_bytes >= L.bytes) return true;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+    (void)hipGetLastError();
+    return false;
+  }
+  char* w = nullptr;
+  if (part_workspace(t, L, st, nullptr, 0, &w) != BHT_OK) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return true;
 }
 
 // *w <- the workspace for layout L: the caller's ws (of ws_bytes), or, when
@@ -735,15 +783,13 @@ void launch_radix(const PartPlan& P, const PartMeta& M, const PartLayout& L, con
                   uint32_t* status, hipStream_t st) {
   void (*hist)(PartPassT<T>);
   void (*scatter)(PartPassT<T>);
-  void (*scatter_lines)(PartPassT<T>) = nullptr;
-  if constexpr (sizeof(T) == 4) {
-    hist = part_hist_kernel<uint32_t>;
-    scatter = part_scatter_kernel<uint32_t>;
-    scatter_lines = part_scatter_lines_kernel<uint32_t>;
-  } else {
-    hist = part_hist64_kernel;
-    scatter = part_scatter64_kernel;
-    scatter_lines = part_scatter_lines_kernel<uint64_t>;
+  void (*scatter_lines)(PartPassT<T>);
+  hist = part_hist_kernel<T, 16>;
+  scatter = part_scatter_kernel<T, 16>;
+  scatter_lines = part_scatter_lines_kernel<T>;
+  if (P.small_chunks) {
+    hist = part_hist_kernel<T, 4>;
+    scatter = part_scatter_kernel<T, 4>;
   }
   // The second pass's chunks are cut for its scatter's rounds of resident
   // blocks.
@@ -879,7 +925,10 @@ bht_status build32_partitioned(bht_table* t, const uint32_t* keys, const uint32_
   ba.cap = K.iceberg ? std::min(t->params.iht_threshold, t->b) : t->b;
   ba.P = P;
   ba.M = M;
-  reinterpret_cast<void (*)(BinArgs)>(const_cast<void*>(K.place))
+  const uint64_t bin = (uint64_t)t->b << P.bin_shift;
+  const void* place = bin <= kSmallBinSlots ? K.place_small
+                      : bin <= 2 * kSmallBinSlots ? K.place_mid : K.place;
+  reinterpret_cast<void (*)(BinArgs)>(const_cast<void*>(place))
       <<<P.nbins, kBinBlock, 0, st>>>(ba);
   if (K.iceberg) {
     IcebergOverflowArgs ia;
@@ -949,7 +998,9 @@ bht_status build32_enqueue(bht_table* t, const uint32_t* keys, const uint32_t* v
   t->built = false;
   t->pending_partitioned = false;
   t->counted_build_probes = 0;
-  if (use_partitioned(t, n, probe_total != nullptr)) return build32_partitioned(t, keys, vals, n, st);
+  if (use_partitioned(t, n, probe_total != nullptr) ||
+      use_small_partitioned(t, n, probe_total != nullptr, st))
+    return build32_partitioned(t, keys, vals, n, st);
   bht_status s = launch_fill(t, st);
   if (s != BHT_OK) return s;
   if (n) {
@@ -1727,11 +1778,13 @@ bht_status bht_batch_create(const bht_batch_entry* entries, uint32_t count, uint
 #undef BHT_BATCH_CASE
   if (!bk) return fail(BHT_ERR_UNSUPPORTED, "no batched kernel for this bucket size and tile");
   const void* pk = nullptr;
+  const void* pk_small = nullptr;
   const void* ok = nullptr;
   const void* ok_both = nullptr;
 #define BHT_BATCH_PCASE(B_, W_)                                   \
   if (t0->b == B_ && t0->tile == W_) {                            \
-    pk = (const void*)batch_place_kernel<B_>;                     \
+    pk = (const void*)batch_place_kernel<B_, bin_slots<B_>()>;    \
+    pk_small = (const void*)batch_place_kernel<B_, kSmallBinSlots>; \
     ok = (const void*)batch_overflow_kernel<B_, false>;           \
     ok_both = (const void*)batch_overflow_kernel<B_, true>;       \
   }
@@ -1797,7 +1850,11 @@ bht_status bht_batch_create(const bht_batch_entry* entries, uint32_t count, uint
     // Partitioned build: every table in one radix pass (at most kMaxFan bins
     // of bin_slots / b buckets each), fewer than 2^32 pairs in all, and no
     // table asks for the concurrent build.
-    const uint64_t R = bin_slots<16>() / t0->b;
+    // Tables of at most 1,024 small bins take those.
+    uint64_t most = 0;
+    for (uint32_t i = 0; i < count; ++i) most = std::max(most, entries[i].table->m);
+    const bool small_bins = most * t0->b <= (uint64_t)kMaxFan * kSmallBinSlots;
+    const uint64_t R = (small_bins ? kSmallBinSlots : bin_slots<16>()) / t0->b;
     uint64_t n_all = 0, bins = 0, counters = 0;
     bool part = pk != nullptr;
     for (uint32_t i = 0; i < count && part; ++i) {
@@ -1869,7 +1926,7 @@ bht_status bht_batch_create(const bht_batch_entry* entries, uint32_t count, uint
         if (e == hipSuccess)
           e = hipMemcpy(w + o_bt, bin_table.data(), 4 * bins, hipMemcpyHostToDevice);
         b->partitioned = e == hipSuccess;
-        b->place_kernel = pk;
+        b->place_kernel = small_bins ? pk_small : pk;
         b->overflow_kernel = small_overflow(ok, bins) ? ok_both : ok;
         pa.splits = overflow_parts(overflow_grid(b->overflow_kernel, ~0ull), bins);
       } else {

@@ -124,7 +124,7 @@ __global__ __launch_bounds__(kBlock) void batch_find_kernel(const BatchTable* __
 // Bins of all tables are numbered globally (table t owns bins
 // [bin_off_t, bin_off_t + nbins_t)); placement and overflow insertion run
 // over the global bins.  Work items of the counting and scatter kernels are
-// (table, chunk of at most 65,536 pairs); the partitioned pairs live in a
+// (table, chunk of at most kBatchChunk pairs); the partitioned pairs live in a
 // workspace where table t's pairs start at key_off_t.
 
 struct BatchPart {
@@ -176,7 +176,7 @@ __global__ __launch_bounds__(kPassBlock) void batch_part_hist_kernel(BatchPartAr
   const Hash32 H = T.H;
   const uint32_t shift = a.bin_shift;
   const bool sentinel =
-      hist_range(T.keys, c.start, c.start + c.count, P.nbins,
+      hist_range<8>(T.keys, c.start, c.start + c.count, P.nbins,
                  [&](uint32_t k) { return hash32(H, 0, k) >> shift; },
                  a.hist + P.hist_off + (uint64_t)c.local * P.nbins, a.total + P.bin_off);
   if (sentinel) atomicOr(a.status + c.table, kFlagSentinel);
@@ -203,14 +203,14 @@ __global__ __launch_bounds__(kPassBlock, kScatterBlocksPerCU) void batch_part_sc
   const BatchPart P = a.parts[c.table];
   const Hash32 H = T.H;
   const uint32_t shift = a.bin_shift;
-  scatter_range(T.keys, T.vals, c.start, c.start + c.count, P.nbins,
+  scatter_range<16>(T.keys, T.vals, c.start, c.start + c.count, P.nbins,
                 [&](uint32_t k) { return hash32(H, 0, k) >> shift; },
                 a.hist + P.hist_off + (uint64_t)c.local * P.nbins, a.cursor + P.bin_off, a.keys,
                 a.vals);
 }
 
 // One block per global bin.
-template <int B>
+template <int B, int S>
 __global__ __launch_bounds__(kBinBlock) void batch_place_kernel(BatchPartArgs a) {
   const uint32_t g = blockIdx.x;
   const uint32_t t = a.bin_table[g];
@@ -218,7 +218,7 @@ __global__ __launch_bounds__(kBinBlock) void batch_place_kernel(BatchPartArgs a)
   const uint32_t R = 1u << a.bin_shift;
   const uint64_t first = (uint64_t)(g - a.parts[t].bin_off) * R;
   const uint32_t nb = (uint64_t)T.H.m - first < (uint64_t)R ? (uint32_t)(T.H.m - first) : R;
-  const uint32_t ovf = place_bin<B>(T.slots, a.keys, a.vals, T.H, R, first, nb, a.bin_start[g],
+  const uint32_t ovf = place_bin<B, true, S>(T.slots, a.keys, a.vals, T.H, R, first, nb, a.bin_start[g],
                                     a.bin_len[g], T.max_chain, T.rng_seed, g, (uint32_t)B,
                                     a.status + t);
   if (threadIdx.x == 0) a.ovf_len[g] = ovf;

@@ -73,12 +73,14 @@ constexpr int kPartSub = BHT_PASS_PER * kPassBlock;   // pairs per sub-tile (4-b
 // digit) range, so larger chunks pad less: 1.7% and 3.2% of the pairs at
 // 2^28 against 3.4% and 6.3% with 64 K chunks, and the padded first pass
 // fits the slot array up to LF 0.96 at 2^28 pairs, 0.98 at 2^27); the
-// batched build keeps 64 K-pair chunks.
+// batched build, whose tables are small, cuts chunks of one sub-tile (16 K
+// pairs): at 64 K, 12 M pairs in 256 tables were 371 blocks of one per CU,
+// 83 us for the scatter and 27 for the counts instead of 62 and 17.
 #ifndef BHT_PART_CHUNK_SUBS
 #define BHT_PART_CHUNK_SUBS 8
 #endif
 constexpr uint32_t kPartChunkMax = BHT_PART_CHUNK_SUBS * kPartSub;
-constexpr uint32_t kBatchChunk = 4 * kPartSub;
+constexpr uint32_t kBatchChunk = kPartSub;
 constexpr uint32_t kMaxFan = 1024;                     // digits of the first pass, at most
 constexpr uint32_t kFan2 = 256;                        // digits of the second pass
 constexpr int kLineSub = 8 * kPassBlock;               // pairs per sub-tile of the line-writing scatter
@@ -91,6 +93,11 @@ constexpr int kBinPer = 16;                            // pairs per thread per r
 // a 4-byte load counter per bucket beside them, so its bins are halved).
 template <int B>
 constexpr int bin_slots() { return B == 1 ? 4096 : 8192; }
+// Bins of small tables are placed by kernels compiled for 2,048 and 4,096
+// slots: with the LDS and the 16 pairs per thread of the largest bins, 569
+// bins of 2,048 slots (2^20 pairs) took two rounds of two blocks per CU and
+// 18 us, against 8-10.
+constexpr int kSmallBinSlots = 2048;
 
 struct PartPlan {
   Hash32 H;             // first hash (index 0) and bucket count, 32-bit keys
@@ -103,6 +110,7 @@ struct PartPlan {
   uint32_t lines1;      // the first pass writes whole lines (ranges padded with the empty key)
   uint32_t lines2;      // the same for the second pass
   uint32_t chunks2_cap; // second-pass chunks the workspace holds
+  uint32_t small_chunks; // sub-tiles of 4 pairs per thread
   uint32_t resident2;   // second-pass scatter blocks resident at once (0: unknown)
 };
 
@@ -299,14 +307,14 @@ __device__ __forceinline__ bool reserved_key(uint64_t k) { return k >= ~0ull - 1
 // Pairs staged per sub-tile for keys and values of type T (LDS holds two
 // sub-tile arrays of T: 128 KB for 4- and for 8-byte words).
 template <typename T>
-constexpr int sub_tile() { return sizeof(T) == 4 ? kPartSub : kPartSub / 2; }
+constexpr int sub_tile(int per) { return per * kPassBlock / (sizeof(T) == 4 ? 1 : 2); }
 
 // Digit counts of the pairs [begin, end) of in_k: stored in hrow (for the
 // scatter's reservations) and added to tot, rounded up to whole lines of
 // pad_to words when the scatter writes lines (pad_to = 0: not rounded);
 // returns whether the range held a reserved key.  With skip_pads, empty
 // keys are padding and not counted.  Every thread of the block calls it.
-template <typename T, typename DigitFn>
+template <int U, typename T, typename DigitFn>
 __device__ __forceinline__ bool hist_range(const T* __restrict__ in_k, uint64_t begin,
                                            uint64_t end, uint32_t fan, DigitFn digit,
                                            uint32_t* __restrict__ hrow,
@@ -316,7 +324,6 @@ __device__ __forceinline__ bool hist_range(const T* __restrict__ in_k, uint64_t 
   for (uint32_t d = threadIdx.x; d < fan; d += kPassBlock) cnt[d] = 0;
   __syncthreads();
   bool sentinel = false;
-  constexpr int U = 8;
   // 32-bit offsets from the range's start (a range is one chunk, under 2^32
   // pairs), so the address arithmetic stays in single registers
   const T* __restrict__ kb = in_k + begin;
@@ -356,7 +363,7 @@ __device__ __forceinline__ bool hist_range(const T* __restrict__ in_k, uint64_t 
 
 // Digit counts of one chunk: stored per chunk (for the scatter's
 // reservations) and added to the range's digit totals.
-template <typename T>
+template <typename T, int PAIRS>
 __global__ __launch_bounds__(kPassBlock) void part_hist_kernel(PartPassT<T> p) {
   uint32_t seg;
   uint64_t begin, end;
@@ -365,7 +372,7 @@ __global__ __launch_bounds__(kPassBlock) void part_hist_kernel(PartPassT<T> p) {
   unsigned long long* tot = p.level == 1 ? p.M.total1 : p.M.total2 + (uint64_t)seg * kFan2;
   const PartPlan& P = p.P;
   const uint32_t level = p.level;
-  const bool sentinel = hist_range(p.in_k, begin, end, p.fan,
+  const bool sentinel = hist_range<PAIRS < 8 ? PAIRS : 8>(p.in_k, begin, end, p.fan,
                                    [&](T k) { return part_digit(P, level, k); }, h, tot,
                                    p.padded != 0, p.lines ? line_words<T>() : 0u);
   if (level == 1 && sentinel) atomicOr(p.status, kFlagSentinel);
@@ -542,7 +549,7 @@ __global__ __launch_bounds__(kPartBlock) void part_scan2_kernel(PartPlan P, Part
 // current one is ranked, so they overlap the on-chip work.  Positions are
 // below 2^32 (the partitioned path takes fewer than 2^32 pairs).  Every
 // thread of the block calls it.
-template <typename T, typename DigitFn>
+template <int PAIRS, typename T, typename DigitFn>
 __device__ __forceinline__ void scatter_range(const T* __restrict__ in_k,
                                               const T* __restrict__ in_v, uint64_t begin,
                                               uint64_t end, uint32_t fan, DigitFn digit,
@@ -550,7 +557,7 @@ __device__ __forceinline__ void scatter_range(const T* __restrict__ in_k,
                                               unsigned long long* __restrict__ cur,
                                               T* __restrict__ out_k, T* __restrict__ out_v,
                                               bool padded = false) {
-  constexpr int SUB = sub_tile<T>();
+  constexpr int SUB = sub_tile<T>(PAIRS);
   constexpr int PER = SUB / kPassBlock;
   __shared__ T sk[SUB];
   __shared__ T sv[SUB];
@@ -673,7 +680,7 @@ __device__ __forceinline__ void scatter_range(const T* __restrict__ in_k,
   }
 }
 
-template <typename T>
+template <typename T, int PAIRS>
 __global__ __launch_bounds__(kPassBlock, kScatterBlocksPerCU) void part_scatter_kernel(PartPassT<T> p) {
   uint32_t seg;
   uint64_t begin, end;
@@ -682,7 +689,7 @@ __global__ __launch_bounds__(kPassBlock, kScatterBlocksPerCU) void part_scatter_
   unsigned long long* cur = p.level == 1 ? p.M.cursor1 : p.M.cursor2 + (uint64_t)seg * kFan2;
   const PartPlan& P = p.P;
   const uint32_t level = p.level;
-  scatter_range(p.in_k, p.in_v, begin, end, p.fan,
+  scatter_range<PAIRS>(p.in_k, p.in_v, begin, end, p.fan,
                 [&](T k) { return part_digit(P, level, k); }, h, cur, p.out_k, p.out_v,
                 p.padded != 0);
 }
@@ -917,7 +924,7 @@ struct BinArgs {
 // of the table (nb <= R <= slots / B); its pairs are keys/vals[s0, s0 +
 // len).  Returns (in every thread) the number of pairs written back; raises
 // flags in *status.  Every thread of the block calls it.
-template <int B, bool EVICT = true>
+template <int B, bool EVICT, int S>
 __device__ __forceinline__ uint32_t place_bin(uint64_t* __restrict__ slots,
                                               uint32_t* __restrict__ keys,
                                               uint32_t* __restrict__ vals, const Hash32& H,
@@ -925,7 +932,7 @@ __device__ __forceinline__ uint32_t place_bin(uint64_t* __restrict__ slots,
                                               uint64_t s0, uint64_t len, uint32_t max_chain,
                                               uint32_t rng_seed, uint32_t salt, uint32_t cap,
                                               uint32_t* __restrict__ status) {
-  constexpr int S = bin_slots<B>();
+  constexpr int PER = S / kBinBlock < kBinPer ? S / kBinBlock : kBinPer;
   constexpr int RMAX = S / B;                    // buckets per bin, at most
   __shared__ u64x2 tbl2[S / 2];
   // [RMAX + lane]: counter of a lane without a pair (one per lane, so a
@@ -947,17 +954,17 @@ __device__ __forceinline__ uint32_t place_bin(uint64_t* __restrict__ slots,
   uint32_t* __restrict__ vb = vals + s0;
   const uint32_t n_bin = (uint32_t)len;
   __syncthreads();
-  for (uint32_t r0 = 0; r0 < n_bin; r0 += kBinBlock * kBinPer) {
-    uint32_t k[kBinPer], v[kBinPer], full[kBinPer];
+  for (uint32_t r0 = 0; r0 < n_bin; r0 += kBinBlock * PER) {
+    uint32_t k[PER], v[PER], full[PER];
 #pragma unroll
-    for (int j = 0; j < kBinPer; ++j) {
+    for (int j = 0; j < PER; ++j) {
       // branch-free loads: offsets past the end re-read the bin's last pair
       const uint32_t i = r0 + j * kBinBlock + threadIdx.x;
       k[j] = kb[i < n_bin ? i : n_bin - 1];
       v[j] = vb[i < n_bin ? i : n_bin - 1];
     }
 #pragma unroll
-    for (int j = 0; j < kBinPer; ++j) {
+    for (int j = 0; j < PER; ++j) {
       full[j] = ~0u;
       const uint32_t i = r0 + j * kBinBlock + threadIdx.x;
       // No branch per pair: a lane without a pair (past the bin's end, or
@@ -984,7 +991,7 @@ __device__ __forceinline__ uint32_t place_bin(uint64_t* __restrict__ slots,
     // all exchanges first, then the stores of the evicted pairs (a store
     // between two exchanges would make each exchange wait for it)
 #pragma unroll
-    for (int j = 0; j < kBinPer; ++j) {
+    for (int j = 0; j < PER; ++j) {
       if (full[j] != ~0u) {
         if constexpr (!EVICT) {
           full[j] = atomicAdd(&ovf, 1u);
@@ -1002,7 +1009,7 @@ __device__ __forceinline__ uint32_t place_bin(uint64_t* __restrict__ slots,
       }
     }
 #pragma unroll
-    for (int j = 0; j < kBinPer; ++j) {
+    for (int j = 0; j < PER; ++j) {
       if (full[j] != ~0u) {
         kb[full[j]] = k[j];
         vb[full[j]] = v[j];
@@ -1018,14 +1025,14 @@ __device__ __forceinline__ uint32_t place_bin(uint64_t* __restrict__ slots,
   return ovf;
 }
 
-template <int B, bool EVICT = true>
+template <int B, bool EVICT, int S>
 __global__ __launch_bounds__(kBinBlock) void bin_place_kernel(BinArgs a) {
   const uint32_t R = 1u << a.P.bin_shift;        // buckets per bin of this plan
   const uint32_t bin = blockIdx.x;
   const uint64_t first = (uint64_t)bin * R;
   const uint32_t nb = (uint64_t)a.P.H.m - first < (uint64_t)R ? (uint32_t)(a.P.H.m - first) : R;
   const uint32_t ovf =
-      place_bin<B, EVICT>(a.slots, a.keys, a.vals, a.P.H, R, first, nb, a.M.bin_start[bin],
+      place_bin<B, EVICT, S>(a.slots, a.keys, a.vals, a.P.H, R, first, nb, a.M.bin_start[bin],
                           a.M.bin_len[bin], a.max_chain, a.rng_seed, bin, a.cap, a.status);
   if (threadIdx.x == 0) a.M.ovf_len[bin] = ovf;
 }

@@ -22,33 +22,6 @@ namespace bht {
 constexpr int kBin64Slots = 4096;      // 16-byte slots of one bin (64 KB of LDS)
 constexpr int kBin64Per = 8;           // pairs per thread per placement round
 
-__global__ __launch_bounds__(kPassBlock) void part_hist64_kernel(PartPass64 p) {
-  uint32_t seg;
-  uint64_t begin, end;
-  if (!part_chunk(p, blockIdx.x, &seg, &begin, &end)) return;
-  uint32_t* h = (p.level == 1 ? p.M.hist1 : p.M.hist2) + (uint64_t)blockIdx.x * p.fan;
-  unsigned long long* tot = p.level == 1 ? p.M.total1 : p.M.total2 + (uint64_t)seg * kFan2;
-  const PartPlan& P = p.P;
-  const uint32_t level = p.level;
-  const bool sentinel = hist_range(p.in_k, begin, end, p.fan,
-                                   [&](uint64_t k) { return part_digit(P, level, k); }, h, tot,
-                                   p.padded != 0, p.lines ? line_words<uint64_t>() : 0u);
-  if (level == 1 && sentinel) atomicOr(p.status, kFlagSentinel);
-}
-
-__global__ __launch_bounds__(kPassBlock, kScatterBlocksPerCU) void part_scatter64_kernel(PartPass64 p) {
-  uint32_t seg;
-  uint64_t begin, end;
-  if (!part_chunk(p, blockIdx.x, &seg, &begin, &end)) return;
-  const uint32_t* h = (p.level == 1 ? p.M.hist1 : p.M.hist2) + (uint64_t)blockIdx.x * p.fan;
-  unsigned long long* cur = p.level == 1 ? p.M.cursor1 : p.M.cursor2 + (uint64_t)seg * kFan2;
-  const PartPlan& P = p.P;
-  const uint32_t level = p.level;
-  scatter_range(p.in_k, p.in_v, begin, end, p.fan,
-                [&](uint64_t k) { return part_digit(P, level, k); }, h, cur, p.out_k, p.out_v,
-                p.padded != 0);
-}
-
 struct BinArgs64 {
   uint64_t* slots;               // the table: key word, value word per slot
   uint64_t* keys;                // partitioned pairs; evicted pairs are written back in place

@@ -352,3 +352,44 @@ def test_overflow_chains_by_hash_count(h, b, n, lf):
     part, evicted, probes = B.bht_build_stats(t.handle)
     assert part and evicted == int(np.maximum(counts - b, 0).sum()) and probes >= evicted
     t.close()
+
+
+@pytest.mark.parametrize("b,n,lf", [(16, 1 << 15, 0.9), (16, (1 << 15) - 1, 0.9), (16, 100003, 0.9),
+                                    (16, (1 << 20) + 5, 0.9), (16, 2000003, 0.9), (32, 65537, 0.95),
+                                    (8, 1 << 15, 0.85), (4, 131072, 0.8), (1, 131071, 0.8)])
+def test_default_build_around_its_thresholds(b, n, lf):
+    """Default builds on both sides of the sizes where the partitioned path,
+    its small sub-tiles (up to 2^20 pairs) and its bins of 2,048, 4,096 and
+    8,192 slots begin; a captured first build, which cannot allocate the
+    workspace, still builds."""
+    import torch
+    B = bht()
+    scheme = "cht1" if b == 1 else "bcht"
+    keys, vals = workload(n, 83)
+    dk, dv = dev(keys), dev(vals)
+    for s in range(10):
+        params = oracle.params_for(scheme, n, lf, 8300 + s, b=b, max_chain=512)
+        t, st = build_partitioned(params, keys, vals, mode="auto")
+        if st == B.BHT_OK:
+            break
+        t.close()
+    else:
+        pytest.fail("no default build succeeded")
+    assert B.bht_build_stats(t.handle)[0] == (n >= (1 << 15 if b >= 8 else 1 << 17))
+    check_table(t, params, keys, vals)
+    t.close()
+    if n >= 1 << 18:
+        return
+    t = B.Table(params.m * b, b, scheme, params.a, params.c, rng_seed=params.rng_seed,
+                max_chain=512)
+    side = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        B.bht_build_async(t.handle, dk, dv, stream=side)
+    for _ in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+    assert B.bht_build_wait(t.handle) == B.BHT_OK
+    assert not B.bht_build_stats(t.handle)[0]
+    check_table(t, params, keys, vals)
+    t.close()
