@@ -20,6 +20,7 @@
 #include "bht_wide.hpp"
 #include "bht_batch.hpp"
 #include "bht_partition.hpp"
+#include "bht_small.hpp"
 #include "bht_wide_partition.hpp"
 #include "bht_iceberg_partition.hpp"
 
@@ -729,6 +730,22 @@ bool use_small_partitioned(bht_table* t, uint64_t n, bool counting, hipStream_t 
   return true;
 }
 
+// The one-workgroup build of a table that fits LDS, or null: the default of
+// cuckoo tables that small, whatever the number of pairs.
+const void* small_build(const bht_table* t, bool counting) {
+  if (counting || t->build_mode != BHT_BUILD_AUTO || t->key_bits != 32) return nullptr;
+  if (t->scheme != BHT_BCHT && t->scheme != BHT_CHT1) return nullptr;
+#define BHT_SCASE(B_) \
+  if (t->b == B_ && t->words <= (uint64_t)small_slots<B_>()) return (const void*)small_build_kernel<B_>;
+  BHT_SCASE(1)
+  BHT_SCASE(4)
+  BHT_SCASE(8)
+  BHT_SCASE(16)
+  BHT_SCASE(32)
+#undef BHT_SCASE
+  return nullptr;
+}
+
 // *w <- the workspace for layout L: the caller's ws (of ws_bytes), or, when
 // ws is null, the table's own, allocated on first use and grown as needed.
 bht_status part_workspace(bht_table* t, const PartLayout& L, hipStream_t st, void* ws,
@@ -998,11 +1015,16 @@ bht_status build32_enqueue(bht_table* t, const uint32_t* keys, const uint32_t* v
   t->built = false;
   t->pending_partitioned = false;
   t->counted_build_probes = 0;
+  const void* small = n ? small_build(t, probe_total != nullptr) : nullptr;
   if (use_partitioned(t, n, probe_total != nullptr) ||
-      use_small_partitioned(t, n, probe_total != nullptr, st))
+      (!small && use_small_partitioned(t, n, probe_total != nullptr, st)))
     return build32_partitioned(t, keys, vals, n, st);
-  bht_status s = launch_fill(t, st);
-  if (s != BHT_OK) return s;
+  if (small) {
+    ks.build = small;
+  } else {
+    bht_status s = launch_fill(t, st);
+    if (s != BHT_OK) return s;
+  }
   if (n) {
     // Load-balanced placements (power of two, iceberg) decide from bucket
     // loads read before the lane's CAS; with every pair of a small table in
@@ -1011,7 +1033,8 @@ bht_status build32_enqueue(bht_table* t, const uint32_t* keys, const uint32_t* v
     // placement matches the serial rule; large tables still fill the device.
     const uint64_t grid_items =
         ks.kind == Kind::Cuckoo ? n : (n + kLbPairsPerLane - 1) / kLbPairsPerLane;
-    const int grid = grid_for(ks.build, grid_items, t->grid_blocks);
+    const int grid = small ? 1 : grid_for(ks.build, grid_items, t->grid_blocks);
+    const int block = small ? kSmallBlock : kBlock;
     if (t->timing) HIP_TRY(hipEventRecord(t->ev[0], st));
     if (ks.kind == Kind::Cuckoo || ks.kind == Kind::LoadBalanced) {
       BuildArgs32 g;
@@ -1025,7 +1048,7 @@ bht_status build32_enqueue(bht_table* t, const uint32_t* keys, const uint32_t* v
       g.max_chain = t->params.max_chain;
       g.rng_seed = t->params.rng_seed;
       reinterpret_cast<void (*)(BuildArgs32)>(const_cast<void*>(ks.build))
-          <<<grid, kBlock, 0, st>>>(g);
+          <<<grid, block, 0, st>>>(g);
     } else {
       SchemeArgs32 g;
       g.slots = t->d_slots;

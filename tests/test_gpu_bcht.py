@@ -329,3 +329,48 @@ def test_parallel_probing_reads_every_candidate(b, h):
     expect[5] = 0
     np.testing.assert_array_equal(host_u8(pr), expect)
     t.close()
+
+
+@pytest.mark.parametrize("b,n,slots", [
+    (16, 14700, 16384), (16, 14700, 16400),     # the largest table built by one workgroup; one more
+    (16, 1, 16), (16, 1025, 1200), (16, 15800, 16384), (8, 13500, 16384), (4, 12000, 16384),
+    (32, 15000, 16384), (1, 9000, 12288), (1, 9000, 12289), (1, 333, 401), (16, 6000, 16384),
+])
+def test_small_table_build(b, n, slots):
+    """Tables around the size one workgroup builds in LDS: every layout is
+    valid and every lookup equals brute force; a reserved key and a build
+    that cannot succeed are reported, and the table rebuilds after either."""
+    import torch
+    B = bht()
+    scheme = "cht1" if b == 1 else "bcht"
+    keys, vals = workload(n, 91)
+    for s in range(10):
+        a, c = datagen.hash_constants(9100 + s, 3)
+        p = oracle.Params(scheme=scheme, b=b, m=-(-slots // b), h=3, a=a, c=c,
+                          rng_seed=datagen.rng_seed(9100 + s), max_chain=512)
+        t = B.Table(p.m * b, b, scheme, p.a, p.c, rng_seed=p.rng_seed, max_chain=512)
+        st = t.build(dev(keys), dev(vals))
+        if st == B.BHT_OK:
+            break
+        t.close()
+    else:
+        pytest.fail("no build succeeded")
+    bad = keys.copy()
+    bad[n // 2] = 0xFFFFFFFF
+    assert t.build(dev(bad), dev(vals)) == B.BHT_ERR_SENTINEL_KEY
+    if n > 2 * b:
+        B.bht_reseed(t.handle, B.make_params([5, 5, 5], [9, 9, 9]))
+        same = np.arange(n, dtype=np.uint64) * p.m          # one bucket for every pair
+        if same.max() < 4294967291:
+            st = t.build(dev(same.astype(np.uint32)), dev(vals))
+            assert st == B.BHT_ERR_BUILD_FAILED
+    B.bht_reseed(t.handle, B.make_params(p.a, p.c, rng_seed=p.rng_seed, max_chain=512))
+    assert t.build(dev(keys), dev(vals)) == B.BHT_OK
+    assert oracle.check32(p, t.download(), keys, vals) == (0, "ok")
+    q = datagen.mixed_queries(n, max(2 * n, 64), 0.5, 91)
+    v, f = t.find(dev(q))
+    torch.cuda.synchronize()
+    ev, ef = oracle.brute_find32(keys, vals, q)
+    np.testing.assert_array_equal(host_u8(f), ef)
+    np.testing.assert_array_equal(host_u32(v), ev)
+    t.close()
