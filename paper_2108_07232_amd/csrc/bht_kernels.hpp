@@ -181,6 +181,15 @@ __global__ void fill_empty_kernel(uint64_t* __restrict__ slots, uint64_t words,
   if ((words & 1) && gtid == 0) slots[words - 1] = kEmptyPair;
 }
 
+// Copies the build status to host memory the calling thread polls: the
+// words, then the flag after them (one lane, released to the host).
+constexpr int kStatusWords = 8;
+__global__ void publish_status_kernel(const uint32_t* __restrict__ status, uint32_t* host) {
+  if (threadIdx.x != 0) return;
+  for (int i = 0; i < kStatusWords; ++i) host[i] = status[i];
+  __hip_atomic_store(host + kStatusWords, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Adds the per-query probe counts of an instrumented find to a 64-bit total
 // (one block-wide sum, then one atomic per block).
 __global__ void probe_sum_kernel(const uint8_t* __restrict__ probes, uint64_t n,

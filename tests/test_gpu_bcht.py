@@ -374,3 +374,37 @@ def test_small_table_build(b, n, slots):
     np.testing.assert_array_equal(host_u8(f), ef)
     np.testing.assert_array_equal(host_u32(v), ev)
     t.close()
+
+
+def test_builds_from_several_threads_and_streams():
+    """Threads that wait for builds at the same time, each on a stream of
+    its own: every thread reads its own table's status."""
+    import threading
+    import torch
+    B = bht()
+    good, bad = workload(5000, 95), workload(40000, 96)
+    bad[0][77] = 0xFFFFFFFF
+    params = [oracle.params_for("bcht", len(d[0]), 0.8, 9500 + i) for i, d in enumerate((good, bad))]
+    data = [(dev(k), dev(v)) for k, v in (good, bad)]
+    torch.cuda.synchronize()
+    wrong = []
+
+    def work(i):
+        which = i % 2
+        p, (dk, dv) = params[which], data[which]
+        t = B.Table(p.m * p.b, p.b, "bcht", p.a, p.c, rng_seed=p.rng_seed)
+        side = torch.cuda.Stream()
+        expect = B.BHT_ERR_SENTINEL_KEY if which else B.BHT_OK
+        for _ in range(20):
+            st = t.build(dk, dv, stream=side)
+            if st != expect:
+                wrong.append((i, st))
+        side.synchronize()
+        t.close()
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(6)]
+    for th in threads:
+        th.start()
+    for th in threads:
+        th.join()
+    assert not wrong
