@@ -706,8 +706,7 @@ bool use_partitioned(const bht_table* t, uint64_t n, bool counting) {
   return n >= kPartWorkspaceKeys;
 }
 
-bht_status part_workspace(bht_table* t, const PartLayout& L, hipStream_t st, void* ws,
-                          uint64_t ws_bytes, char** w);
+char* table_workspace(bht_table* t, uint64_t bytes, hipStream_t st);
 
 // Whether a cuckoo build below kPartWorkspaceKeys takes the partitioned path.
 bool use_small_partitioned(bht_table* t, uint64_t n, bool counting, hipStream_t st) {
@@ -716,19 +715,7 @@ bool use_small_partitioned(bht_table* t, uint64_t n, bool counting, hipStream_t 
   if (t->build_mode != BHT_BUILD_AUTO || !t->owns_memory) return false;
   PartPlan P;
   if (!part_plan(t, n, &P)) return false;
-  const PartLayout L = part_layout(P, n);
-  if (t->part_bytes >= L.bytes) return true;
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
-    (void)hipGetLastError();
-    return false;
-  }
-  char* w = nullptr;
-  if (part_workspace(t, L, st, nullptr, 0, &w) != BHT_OK) {
-    (void)hipGetLastError();
-    return false;
-  }
-  return true;
+  return table_workspace(t, part_layout(P, n).bytes, st) != nullptr;
 }
 
 // The one-workgroup build of a table that fits LDS, or null: the default of
@@ -1003,6 +990,44 @@ bht_status build32_partitioned(bht_table* t, const uint32_t* keys, const uint32_
   return BHT_OK;
 }
 
+// Power-of-two builds of up to this many pairs take the counted kernel, with
+// at most kP2Lanes pairs under way (at LF 0.8, us, bucket-reading and counted
+// kernel: 5,000 pairs 217 and 22, 100,003 306 and 40, 2^20 328 and 90, 2^22
+// 392 and 268, 2^23 615 and 528; past that its two loads and an atomic beside
+// the stored pair leave the last-level cache: 2^24 1288 and 1306, 2^26 5684
+// and 6951.  2^20 pairs with 48, 64, 96, 128, 256 K lanes: 98, 90, 92, 96,
+// 134).
+constexpr uint64_t kP2CountMaxKeys = 1ull << 23;
+constexpr uint64_t kP2Lanes = 1ull << 16;
+
+// The counted power-of-two build of n pairs into table t, or null.
+const void* p2_count_kernel(const bht_table* t, uint64_t n, bool counting) {
+  if (t->scheme != BHT_BP2HT || counting || !t->owns_memory || n > kP2CountMaxKeys) return nullptr;
+  return t->b == 8    ? (const void*)p2_count_build_kernel<8>
+         : t->b == 16 ? (const void*)p2_count_build_kernel<16>
+         : t->b == 32 ? (const void*)p2_count_build_kernel<32> : nullptr;
+}
+
+// The table's own workspace of at least `bytes`, or null where it is neither
+// at hand nor can be allocated now.
+char* table_workspace(bht_table* t, uint64_t bytes, hipStream_t st) {
+  PartLayout L{};
+  L.bytes = bytes;
+  char* w = nullptr;
+  if (t->part_bytes < bytes) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+      (void)hipGetLastError();
+      return nullptr;
+    }
+  }
+  if (part_workspace(t, L, st, nullptr, 0, &w) != BHT_OK) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  return w;
+}
+
 bht_status build32_enqueue(bht_table* t, const uint32_t* keys, const uint32_t* vals, uint64_t n,
                            unsigned long long* probe_total, void* stream) {
   if (!t) return fail(BHT_ERR_INVALID_ARG, "null table");
@@ -1034,10 +1059,32 @@ bht_status build32_enqueue(bht_table* t, const uint32_t* keys, const uint32_t* v
     // placement matches the serial rule; large tables still fill the device.
     const uint64_t grid_items =
         ks.kind == Kind::Cuckoo ? n : (n + kLbPairsPerLane - 1) / kLbPairsPerLane;
+    // the counts take as much memory as the table, at most
+    const void* p2_kernel = p2_count_kernel(t, n, probe_total != nullptr);
+    const uint64_t count_words = t->m * p2_count_stride(t->b);
+    uint32_t* counts = p2_kernel
+                           ? reinterpret_cast<uint32_t*>(table_workspace(t, count_words * 4, st))
+                           : nullptr;
+    if (counts) {
+      const int clear_grid = (int)std::min<uint64_t>((t->m + kBlock - 1) / kBlock, 4096);
+      p2_clear_kernel<<<clear_grid, kBlock, 0, st>>>(counts, t->m, p2_count_stride(t->b));
+    }
     const int grid = small ? 1 : grid_for(ks.build, grid_items, t->grid_blocks);
     const int block = small ? kSmallBlock : kBlock;
     if (t->timing) HIP_TRY(hipEventRecord(t->ev[0], st));
-    if (ks.kind == Kind::Cuckoo || ks.kind == Kind::LoadBalanced) {
+    if (counts) {
+      P2CountArgs g;
+      g.slots = t->d_slots;
+      g.counts = counts;
+      g.keys = keys;
+      g.vals = vals;
+      g.n = n;
+      g.status = t->d_status;
+      g.H = make_hash32(t->params, t->m, t->params.num_hashes);
+      const int cgrid = grid_for(p2_kernel, std::min(n, kP2Lanes), t->grid_blocks);
+      reinterpret_cast<void (*)(P2CountArgs)>(const_cast<void*>(p2_kernel))
+          <<<cgrid, kBlock, 0, st>>>(g);
+    } else if (ks.kind == Kind::Cuckoo || ks.kind == Kind::LoadBalanced) {
       BuildArgs32 g;
       g.slots = t->d_slots;
       g.keys = keys;

@@ -205,6 +205,81 @@ __global__ __launch_bounds__(kBlock) void p2_build_kernel(SchemeArgs32 g) {
   }
 }
 
+// 4-byte words from one bucket's count to the next: a line of its own, or as
+// many bytes as the bucket if that is less.
+__host__ __device__ constexpr uint32_t p2_count_stride(uint32_t b) { return 2 * b < 32 ? 2 * b : 32; }
+
+// Clears the bucket counts of the build below.
+__global__ void p2_clear_kernel(uint32_t* __restrict__ counts, uint64_t m, uint32_t words) {
+  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += stride)
+    counts[i * words] = 0;
+}
+
+// Power-of-two-choices insertion with one counter per bucket: a pair reads
+// the counts of its two buckets, takes the less loaded one (ties to H0) by
+// raising its count from the value read, which also names its slot, and
+// stores itself there.  A count that has changed comes back from the failed
+// compare-and-swap and the pair chooses again.  Counts only grow, so the
+// bucket taken holds no more pairs than the other one at that moment, as in
+// the serial insertion, however many pairs are under way.
+// The insertion above reads two 128-byte buckets with 8-byte device-scope
+// loads (eight requests and about 700 instructions a round) and keeps one
+// lane per 32 pairs under way; here a placement is two 4-byte loads, one
+// atomic and one store.  Each count has a line of its own: packed 4-byte
+// counts, 32 to a line, took 210 us at 2^20 pairs, 16 and 64 bytes apart 135
+// and 102, a line apart 90 (requests to one line are served in turn).
+struct P2CountArgs {
+  uint64_t* slots;
+  uint32_t* counts;
+  const uint32_t* keys;
+  const uint32_t* vals;
+  uint64_t n;
+  uint32_t* status;
+  Hash32 H;
+};
+
+template <int B>
+__global__ __launch_bounds__(kBlock) void p2_count_build_kernel(P2CountArgs g) {
+  constexpr uint32_t kStride = p2_count_stride(B);
+  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+  uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  uint32_t flags = 0;
+  uint32_t k_next = i < g.n ? g.keys[i] : 0u, v_next = i < g.n ? g.vals[i] : 0u;
+  for (; i < g.n; i += stride) {
+    const uint32_t key = k_next, val = v_next;
+    if (i + stride < g.n) {
+      k_next = g.keys[i + stride];
+      v_next = g.vals[i + stride];
+    }
+    if (key == kEmptyKey) {
+      flags |= kFlagSentinel;
+      continue;
+    }
+    const uint32_t b0 = hash32(g.H, 0, key), b1 = hash32(g.H, 1, key);
+    uint32_t l0 = __hip_atomic_load(g.counts + (uint64_t)b0 * kStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    uint32_t l1 = __hip_atomic_load(g.counts + (uint64_t)b1 * kStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // at most 2 B tries: each failed one has raised a count seen
+    for (;;) {
+      const bool first = l0 <= l1;
+      const uint32_t b = first ? b0 : b1, slot = first ? l0 : l1;
+      if (slot >= (uint32_t)B) {
+        flags |= kFlagFailed;
+        break;
+      }
+      uint32_t seen = slot;
+      if (__hip_atomic_compare_exchange_strong(g.counts + (uint64_t)b * kStride, &seen, slot + 1, __ATOMIC_RELAXED,
+                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+        g.slots[(uint64_t)b * B + slot] = ((uint64_t)val << 32) | key;
+        break;
+      }
+      if (first || b0 == b1) l0 = seen;
+      if (!first || b0 == b1) l1 = seen;
+    }
+  }
+  if (flags) atomicOr(g.status, flags);
+}
+
 enum : uint32_t { kLbRead = 0, kLbPick = 1, kLbWalk = 2, kLbEvict = 3 };
 
 // Load-balanced cuckoo insertion (Section III-A's variation that inserts

@@ -321,3 +321,56 @@ def test_iceberg_build_modes_agree():
     for v, f in results[1:]:
         np.testing.assert_array_equal(v, results[0][0])
         np.testing.assert_array_equal(f, results[0][1])
+
+
+@pytest.mark.parametrize("b,lf,n", [(16, 0.5, 1), (8, 0.6, 63), (16, 0.8, 65536), (16, 0.8, 65537),
+                                    (8, 0.7, 300007), (32, 0.88, 300007), (16, 0.82, 1 << 20)])
+def test_power_of_two_counted_build(b, lf, n):
+    """The build with one counter per bucket, around the pairs it keeps under
+    way (65,536): valid layout, exact lookups, and loads balanced as the serial
+    insertion balances them; a captured first build, which has no memory for
+    the counters, and the instrumented build read the buckets instead."""
+    import torch
+    B = bht()
+    keys, vals = workload(n, 85)
+    dk, dv = dev(keys), dev(vals)
+    for s in range(6):
+        p = oracle.params_for("bp2ht", n, lf, 8500 + s, b=b)
+        t = gpu_table(p)
+        if t.build(dk, dv) == B.BHT_OK:
+            break
+        t.close()
+    else:
+        pytest.fail("no build succeeded")
+
+    def full_buckets(table):
+        slots = table.download().reshape(p.m, b)
+        return int((slots[:, b - 1] != np.uint64(oracle.EMPTY64)).sum())
+
+    assert oracle.check32(p, t.download(), keys, vals)[0] == 0
+    check_find(t, p, keys, vals, datagen.mixed_queries(n, max(n, 64), 0.5, 85))
+    if n > 1000:
+        st, serial, _ = oracle.build32(p, keys, vals)
+        if st == oracle.OK:
+            # a choice between equals is the same, so the number of full
+            # buckets differs by the order of the pairs alone
+            want = int((serial.reshape(p.m, b)[:, b - 1] != np.uint64(oracle.EMPTY64)).sum())
+            assert abs(full_buckets(t) - want) <= 6 * max(want, 25) ** 0.5 + 0.02 * want
+    bad = keys.copy()
+    bad[n // 2] = 0xFFFFFFFF
+    assert t.build(dev(bad), dv) == B.BHT_ERR_SENTINEL_KEY
+    total = torch.zeros(1, dtype=torch.int64, device="cuda")
+    if B.bht_build_counted(t.handle, dk, dv, total) == B.BHT_OK:
+        assert int(total.item()) >= 2 * n
+        assert oracle.check32(p, t.download(), keys, vals)[0] == 0
+    t.close()
+    t = gpu_table(p)
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        B.bht_build_async(t.handle, dk, dv, stream=side)
+    for _ in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+    if B.bht_build_wait(t.handle) == B.BHT_OK:
+        assert oracle.check32(p, t.download(), keys, vals)[0] == 0
+    t.close()
