@@ -235,7 +235,7 @@ bht_status bht_find(const bht_table* t, const uint32_t* d_queries, uint64_t n,
  * not in the paper, whose pairs fit one 64-bit word).  Keys 2^64 - 1 and
  * 2^64 - 2 are reserved (SENTINEL_KEY).  bht_build64 is synchronous like
  * bht_build and follows the table's build_mode: the partitioned path takes
- * builds of at least 2^18 pairs under BHT_BUILD_AUTO (workspace of about
+ * builds of at least 2^15 pairs under BHT_BUILD_AUTO (workspace of about
  * 16 bytes per pair): each bucket's first-choice pairs are placed on chip,
  * the pairs meeting a full first bucket exchange themselves with random
  * residents in rounds ranked by the bucket's load counter, and the evicted
@@ -301,7 +301,7 @@ bht_status bht_get_probe_stats(const bht_table* t, uint64_t* build_probes, uint6
  * reaches the secondary level only once its primary holds iht_threshold
  * pairs, as the threshold rule requires).  BHT_BUILD_AUTO partitions builds of at least 2^15 pairs
  * (2^17 with fewer than 8 slots per bucket, 2^18
- * for two-level iceberg and 64-bit tables, never one-level iceberg ones) into
+ * for two-level iceberg tables, never one-level ones) into
  * tables whose memory the library owns (bht_create); below 2^18 pairs only
  * where the workspace is allocated or can be (not while the stream is
  * captured).

@@ -708,14 +708,16 @@ bool use_partitioned(const bht_table* t, uint64_t n, bool counting) {
 
 char* table_workspace(bht_table* t, uint64_t bytes, hipStream_t st);
 
-// Whether a cuckoo build below kPartWorkspaceKeys takes the partitioned path.
+// Whether a cuckoo build below kPartWorkspaceKeys takes the partitioned path
+// (64-bit pairs, concurrent and partitioned build at LF 0.9, us: 20,000 pairs
+// 83 and 83, 50,000 94 and 67, 100,003 101 and 73, 200,000 121 and 85).
 bool use_small_partitioned(bht_table* t, uint64_t n, bool counting, hipStream_t st) {
   if (counting || n < part_min_keys(t->b) || n >= kPartWorkspaceKeys) return false;
-  if ((t->scheme != BHT_BCHT && t->scheme != BHT_CHT1) || t->key_bits != 32) return false;
+  if (t->scheme != BHT_BCHT && t->scheme != BHT_CHT1) return false;
   if (t->build_mode != BHT_BUILD_AUTO || !t->owns_memory) return false;
   PartPlan P;
   if (!part_plan(t, n, &P)) return false;
-  return table_workspace(t, part_layout(P, n).bytes, st) != nullptr;
+  return table_workspace(t, part_layout(P, n, t->key_bits / 8).bytes, st) != nullptr;
 }
 
 // The one-workgroup build of a table that fits LDS, or null: the default of
@@ -877,10 +879,13 @@ bht_status build64_partitioned(bht_table* t, const uint64_t* keys, const uint64_
   oa.g.rng_seed = (uint32_t)t->params.rng_seed;
   oa.M = M;
   oa.nbins = P.nbins;
-  oa.parts = overflow_parts(resident_blocks((const void*)wide_overflow_kernel<8>, kBlock), P.nbins);
-  const int og = grid_for((const void*)wide_overflow_kernel<8>, (uint64_t)P.nbins * oa.parts * 64,
-                          t->grid_blocks);
-  wide_overflow_kernel<8><<<og, kBlock, 0, st>>>(oa);
+  const bool both = small_overflow((const void*)wide_overflow_kernel<false>, P.nbins);
+  void (*const overflow)(WideOverflowArgs) =
+      both ? wide_overflow_kernel<true> : wide_overflow_kernel<false>;
+  oa.parts = overflow_parts(overflow_grid((const void*)overflow, ~0ull), P.nbins);
+  const int og = t->grid_blocks ? (int)t->grid_blocks
+                                : overflow_grid((const void*)overflow, (uint64_t)P.nbins * oa.parts);
+  overflow<<<og, kBlock, 0, st>>>(oa);
   HIP_TRY(hipGetLastError());
   if (t->timing) HIP_TRY(hipEventRecord(t->ev[1], st));
   t->build_timed = t->timing;
@@ -1653,7 +1658,7 @@ bht_status bht_build64(bht_table* t, const uint64_t* d_keys, const uint64_t* d_v
   t->built = false;
   t->pending_partitioned = false;
   t->counted_build_probes = 0;
-  if (use_partitioned(t, n, false)) {
+  if (use_partitioned(t, n, false) || use_small_partitioned(t, n, false, st)) {
     bht_status s = build64_partitioned(t, d_keys, d_values, n, st);
     if (s != BHT_OK) return s;
     return bht_build_wait(t, stream);

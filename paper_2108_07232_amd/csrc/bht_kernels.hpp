@@ -450,24 +450,29 @@ struct Choices {
   bool has_alt, full;
 };
 
+__device__ __forceinline__ Choices choices_after(const uint32_t (&hv)[4], uint32_t h,
+                                                 uint32_t left) {
+  Choices c = {hv[0], 0u, false, false};
+#pragma unroll
+  for (int i = 3; i >= 0; --i) {
+    if (i < (int)h && hv[i] == left) {
+      const bool more = i + 1 < (int)h;
+      c.at = more ? hv[(i + 1) & 3] : hv[0];
+      c.alt = hv[(i + 2) & 3];
+      c.has_alt = i + 2 < (int)h;
+      c.full = !more;
+    }
+  }
+  return c;
+}
+
 __device__ __forceinline__ Choices next_choices(const Hash32& H, uint32_t key, uint32_t left,
                                                 bool first) {
   uint32_t hv[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) hv[i] = (i < (int)H.h) ? hash32(H, i, key) : 0u;
   if (first) left = hv[0];
-  Choices c = {hv[0], 0u, false, false};
-#pragma unroll
-  for (int i = 3; i >= 0; --i) {
-    if (i < (int)H.h && hv[i] == left) {
-      const bool more = i + 1 < (int)H.h;
-      c.at = more ? hv[(i + 1) & 3] : hv[0];
-      c.alt = hv[(i + 2) & 3];
-      c.has_alt = i + 2 < (int)H.h;
-      c.full = !more;
-    }
-  }
-  return c;
+  return choices_after(hv, H.h, left);
 }
 
 // Occupied slots of one bucket, read by the calling lane alone.

@@ -123,16 +123,14 @@ __device__ __forceinline__ uint32_t next_bucket64(const Hash64& H, uint64_t key,
   return nxt;
 }
 
-enum : uint32_t { kWRead = 0, kWWalk = 1, kWEvict = 2 };
+enum : uint32_t { kWRead = 0, kWWalk = 1, kWEvict = 2, kWMove = 3 };
 
 // Inserts the pairs [r.cursor, r.end) of g.keys / g.vals (one wave's range;
 // the whole wave calls it).  W lanes per tile, one 16-byte slot per lane:
-// B = W = 8 slots per bucket.  EVICTED: each pair was evicted from its
-// first bucket H_0 (one exchange made) and continues at the next one.
-// Bucket reads are added to *probes; returns the lane's status flags.
-template <int W, bool EVICTED>
-__device__ __forceinline__ uint32_t wide_build_range(const WideBuildArgs& g, Range r, uint32_t rng,
-                                                     uint32_t* probes) {
+// B = W = 8 slots per bucket.  Returns the lane's status flags.
+template <int W>
+__device__ __forceinline__ uint32_t wide_build_range(const WideBuildArgs& g, Range r,
+                                                     uint32_t rng) {
   constexpr int B = W;
   const uint32_t lane = __lane_id();
   const uint32_t tb = lane & ~(uint32_t)(W - 1);
@@ -163,10 +161,6 @@ __device__ __forceinline__ uint32_t wide_build_range(const WideBuildArgs& g, Ran
         val = v_new;
         bucket = (uint32_t)hash64(g.H, 0, key);
         chain = 0;
-        if constexpr (EVICTED) {
-          bucket = next_bucket64(g.H, key, bucket);
-          chain = 1;
-        }
         attempts = 0;
         phase = kWRead;
       }
@@ -178,7 +172,6 @@ __device__ __forceinline__ uint32_t wide_build_range(const WideBuildArgs& g, Ran
 
     // Tile read: lane lt loads slot lt (key and value) of each bucket.
     const uint64_t rd = ballot(active && phase == kWRead);
-    *probes += (uint32_t)((rd >> lane) & 1ull);
     uint64_t dk[W];
 #pragma unroll
     for (int j = 0; j < W; ++j) {
@@ -263,11 +256,173 @@ __device__ __forceinline__ uint32_t wide_build_range(const WideBuildArgs& g, Ran
   return flags;
 }
 
+// As next_choices for 64-bit keys.
+__device__ __forceinline__ Choices next_choices64(const Hash64& H, uint64_t key, uint32_t left,
+                                                  bool first) {
+  uint32_t hv[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) hv[i] = (i < (int)H.h) ? (uint32_t)hash64(H, i, key) : 0u;
+  if (first) left = hv[0];
+  return choices_after(hv, H.h, left);
+}
+
+// Insertion of pairs just evicted from their first bucket: the 64-bit
+// counterpart of cuckoo_continue_range (the first of the next two buckets
+// with room, else an eviction at the first of them; every lane reads the
+// keys of its own bucket, and the key of the slot it would evict along with
+// them) over the slot protocol above.  Bucket reads are added to *probes;
+// returns the lane's status flags.
+template <bool BOTH>
+__device__ __forceinline__ uint32_t wide_continue_range(const WideBuildArgs& g, Range r,
+                                                        uint32_t rng, uint32_t* probes_out) {
+  constexpr int B = 8;
+  constexpr uint32_t kRefill = BOTH ? 16 : 1;
+  if (rng == 0) rng = 0x2545F491u;
+  Feed64 fk, fv;
+  fk.init(g.keys, r, kEmpty64);
+  fv.init(g.vals, r, 0ull);
+  bool active = false, has_alt = false, fresh = false;
+  uint64_t key = 0, val = 0, expect = 0;
+  uint32_t bucket = 0, alt = 0, at = 0, chain = 0, slot = 0, phase = kWRead, attempts = 0;
+  uint32_t probes = 0, flags = 0;
+
+  for (;;) {
+    const uint64_t act = ballot(active);
+    if (fk.cursor < fk.end && 64u - (uint32_t)__popcll(act) >= kRefill) {
+      uint64_t idx;
+      const int64_t off = fk.claim(!active, &idx);
+      fv.claim(!active, &idx);
+      const uint64_t k_new = fk.value_at(off);
+      const uint64_t v_new = fv.value_at(off);
+      fk.advance(kEmpty64);
+      fv.advance(0ull);
+      if (off >= 0) {
+        if (k_new >= kBusy64) {
+          flags |= kFlagSentinel;
+        } else {
+          active = fresh = true;
+          key = k_new;
+          val = v_new;
+          chain = 1;
+          attempts = 0;
+          phase = kWMove;
+        }
+      }
+    } else if (act == 0) {
+      break;
+    }
+    if (active && phase == kWMove) {
+      // evicted from its first bucket by the placement, or from bucket `at`
+      const Choices c = next_choices64(g.H, key, at, fresh);
+      fresh = false;
+      bucket = at = c.at;
+      alt = c.alt;
+      has_alt = c.has_alt;
+      rng = xorshift32(rng);
+      if (c.full) {
+        // the key of the slot to evict is learned by the next iteration
+        phase = kWEvict;
+        slot = rng % (uint32_t)B;
+        expect = kBusy64;
+      } else {
+        phase = kWRead;
+      }
+    }
+    if (active && phase == kWRead) {
+      const uint64_t* const keys = g.slots + 2 * (uint64_t)bucket * B;
+      const uint32_t victim = rng % (uint32_t)B;
+      uint64_t last = kEmpty64;
+      if (BOTH && has_alt) last = g.slots[2 * ((uint64_t)alt * B + (B - 1))];
+      // the bucket evictions go to is `at`; past it, its slot's key is learned later
+      const uint64_t seen = keys[2 * victim];
+      uint32_t load = 0;
+      uint64_t k[B];
+#pragma unroll
+      for (int i = 0; i < B; ++i) k[i] = keys[2 * i];
+#pragma unroll
+      for (int i = 0; i < B; ++i) load += k[i] != kEmpty64 ? 1u : 0u;
+      ++probes;
+      if (load < (uint32_t)B) {
+        phase = kWWalk;
+        slot = load;
+      } else if (!has_alt) {
+        phase = kWEvict;
+        slot = victim;
+        expect = bucket == at ? seen : kBusy64;
+      } else {
+        if (BOTH) ++probes;
+        has_alt = false;
+        bucket = alt;
+        if (BOTH && last != kEmpty64) {          // full as well
+          phase = kWEvict;
+          slot = victim;
+          expect = seen;
+        }
+      }
+    }
+
+    if (active && ++attempts > kWideAttemptCap) {
+      flags |= kFlagFailed;
+      active = false;
+    }
+    if (active && phase == kWWalk) {
+      uint64_t* const sk = g.slots + 2 * ((uint64_t)bucket * B + slot);
+      const uint64_t c = cas64(sk, kEmpty64, kBusy64);
+      if (c == kEmpty64) {
+        wait_memory();
+        store_agent(sk + 1, val);
+        wait_memory();
+        store_agent(sk, key);
+        active = false;
+      } else if (++slot == (uint32_t)B) {
+        // the walk proved this bucket full
+        if (has_alt) {
+          has_alt = false;
+          bucket = alt;
+          phase = kWRead;
+        } else {
+          phase = kWEvict;
+          rng = xorshift32(rng);
+          slot = rng % (uint32_t)B;
+          expect = kBusy64;
+        }
+      }
+    } else if (active && phase == kWEvict) {
+      uint64_t* const sk = g.slots + 2 * ((uint64_t)at * B + slot);
+      if (chain >= g.max_chain) {
+        flags |= kFlagFailed;
+        active = false;
+      } else {
+        // learn the slot's key, if it is not known, in the same iteration
+        if (expect == kBusy64) expect = load_key_agent(sk);
+        if (expect == kEmpty64) {
+          // a load from before the slot was filled: the bucket is full
+          expect = kBusy64;
+        } else if (expect != kBusy64) {
+          const uint64_t c = cas64(sk, expect, kBusy64);
+          if (c == expect) {
+            wait_memory();
+            const uint64_t old_v = xchg64(sk + 1, val);
+            wait_memory();
+            store_agent(sk, key);
+            key = expect;
+            val = old_v;
+            ++chain;
+            phase = kWMove;
+          } else {
+            expect = c;                          // retry with the current key
+          }
+        }
+      }
+    }
+  }
+  *probes_out += probes;
+  return flags;
+}
+
 template <int W>
 __global__ __launch_bounds__(kBlock) void wide_build_kernel(WideBuildArgs g) {
-  uint32_t probes = 0;
-  const uint32_t flags = wide_build_range<W, false>(g, wave_range(g.n), g.rng_seed ^ lane_salt(),
-                                                    &probes);
+  const uint32_t flags = wide_build_range<W>(g, wave_range(g.n), g.rng_seed ^ lane_salt());
   if (flags) atomicOr(g.status, flags);
 }
 

@@ -155,7 +155,7 @@ struct WideOverflowArgs {
 
 // Insertion of the pairs evicted during placement, bin by bin from a queue;
 // bucket reads are summed into status words 2-3.
-template <int W>
+template <bool BOTH>
 __global__ __launch_bounds__(kBlock) void wide_overflow_kernel(WideOverflowArgs a) {
   const uint32_t salt = lane_salt();
   uint32_t flags = 0, probes = 0, evicted = 0;
@@ -165,7 +165,7 @@ __global__ __launch_bounds__(kBlock) void wide_overflow_kernel(WideOverflowArgs 
     evicted += (uint32_t)(r.end - r.cursor);
     if (r.cursor < r.end)
       flags |=
-          wide_build_range<W, true>(a.g, r, a.g.rng_seed ^ salt ^ (bin * 0x85EBCA6Bu), &probes);
+          wide_continue_range<BOTH>(a.g, r, a.g.rng_seed ^ salt ^ (bin * 0x85EBCA6Bu), &probes);
   });
   if (flags) atomicOr(a.g.status, flags);
   add_overflow_stats(a.M.stats, a.g.status, evicted, probes);

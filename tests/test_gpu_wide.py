@@ -228,3 +228,32 @@ def test_wide_counted_find_probes_equal_oracle(n, lf, mode):
     with pytest.raises(bht.BhtError):
         bht.bht_find64_counted(t.handle, dev(q), out_v, out_f, None)
     t.close()
+
+
+@pytest.mark.parametrize("n,lf,h", [((1 << 15) - 1, 0.9, 3), (1 << 15, 0.9, 3), (200003, 0.9, 3),
+                                    (50001, 0.6, 2), (50001, 0.95, 4), (1 << 19, 0.95, 3)])
+def test_wide_overflow_chains(n, lf, h):
+    """Default 64-bit builds on both sides of the partitioned path's threshold,
+    with one, two or three buckets left past the one an evicted pair leaves:
+    valid layout (early-exit property included), exact lookups and eviction
+    count."""
+    import paper_2108_07232_amd as bht
+    keys, vals = datagen.unique_keys64(n, 87), datagen.values64(n, 87)
+    for s in range(10):
+        p = oracle.params_for("bcht", n, lf, 8700 + s, b=8, h=h, wide=True, max_chain=512)
+        t = bht.Table(p.m * p.b, 8, "bcht", p.a, p.c, key_bits=64, rng_seed=p.rng_seed,
+                      max_chain=512)
+        if t.build(dev(keys), dev(vals)) == bht.BHT_OK:
+            break
+        t.close()
+    else:
+        pytest.fail("no build succeeded")
+    assert oracle.check64(p, t.download(), keys, vals) == (0, "ok")
+    check(t, keys, vals, datagen.mixed_queries(n, 2 * n, 0.5, 87, wide=True))
+    part, evicted, probes = bht.bht_build_stats(t.handle)
+    assert part == (n >= 1 << 15)
+    if part:
+        h0 = oracle.hash64_many(p.a[0], p.c[0], keys, p.m)
+        counts = np.bincount(h0.astype(np.int64), minlength=p.m)
+        assert evicted == int(np.maximum(counts - 8, 0).sum()) and probes >= evicted
+    t.close()
