@@ -53,6 +53,7 @@ struct bht_table {
   uint32_t build_mode;     // bht_build_mode
   uint32_t iht_early_exit; // iceberg finds stop after a primary below the threshold
   uint32_t unroll;         // chunk-schedule queries per lane per chunk (1 or 2)
+  bool unroll_set;         // ... asked for by the caller
   void* d_part;            // partitioned build workspace (library-owned)
   uint64_t part_bytes;
   bool pending_partitioned;
@@ -158,7 +159,10 @@ int resident_blocks(const void* kernel, int block) {
 // device keeps resident at once (the kernels loop over their share).
 // items_per_lane > 0 asks for at least ceil(items / (256 * items_per_lane))
 // blocks even beyond the resident count: short per-wave ranges let the
-// dispatcher balance waves that finish at different times.
+// dispatcher balance waves that finish at different times.  The queries of
+// the 64-bit and the stable schemes take one chunk per wave (us, resident
+// waves or 16 per lane against 1: 2^22 64-bit queries 146 and 132, 3,000,017
+// iceberg 91 and 81.5, 2^20 power-of-two 30 and 26).
 int grid_for(const void* kernel, uint64_t items, uint32_t fixed = 0, uint64_t items_per_lane = 0) {
   if (fixed) return (int)fixed;
   static std::mutex mu;
@@ -495,6 +499,38 @@ constexpr uint64_t kPartWorkspaceKeys = 1ull << 18;
 #define BHT_ICEBERG_PART_MIN_LOG2 18
 #endif
 constexpr uint64_t kIcebergPartMinKeys = 1ull << BHT_ICEBERG_PART_MIN_LOG2;
+
+// The default query kernel of a cuckoo table for n queries: one wave per 64
+// of them, reading per lane while they leave the device idle.  Null when the
+// caller asked for a schedule, an unroll or a grid, or the launch would
+// exceed 2^32 threads.
+constexpr uint64_t kLaneFindQueries = 1ull << 17;
+
+template <bool C>
+const void* wave_find_t(const bht_table* t, uint64_t n) {
+#define BHT_WCASE(B_, W_)                                                          \
+  if (t->b == B_ && t->tile == W_)                                                 \
+    return n <= kLaneFindQueries ? (const void*)cuckoo_find_lane_kernel<B_, C>     \
+                                 : (const void*)cuckoo_find_wave_kernel<B_, W_, C>;
+  BHT_WCASE(1, 1)
+  BHT_WCASE(4, 4)
+  BHT_WCASE(8, 4)
+  BHT_WCASE(8, 8)
+  BHT_WCASE(16, 4)
+  BHT_WCASE(16, 8)
+  BHT_WCASE(16, 16)
+  BHT_WCASE(32, 8)
+  BHT_WCASE(32, 16)
+#undef BHT_WCASE
+  return nullptr;
+}
+
+const void* wave_find(const bht_table* t, uint64_t n, bool count) {
+  if (t->scheme != BHT_BCHT && t->scheme != BHT_CHT1) return nullptr;
+  if (t->find_schedule != BHT_FIND_DEFAULT || t->unroll_set || t->grid_blocks) return nullptr;
+  if (n > (1ull << 31)) return nullptr;
+  return count ? wave_find_t<true>(t, n) : wave_find_t<false>(t, n);
+}
 
 struct PartKernels {
   const void* place;
@@ -1137,7 +1173,11 @@ bht_status find32_enqueue(const bht_table* t, const uint32_t* q, uint64_t n, uin
   if (!pick(t, t->tile, t->find_schedule, probes != nullptr, &ks))
     return fail(BHT_ERR_UNSUPPORTED, "no kernel for this bucket size and tile width");
   hipStream_t st = as_stream(stream);
-  const int grid = grid_for(ks.find, n, t->grid_blocks, ks.chunk ? 16 : 0);
+  const void* wave = wave_find(t, n, probes != nullptr);
+  if (wave) ks.find = wave;
+  const int grid = wave ? (int)((n + kBlock - 1) / kBlock)
+                        : grid_for(ks.find, n, t->grid_blocks,
+                                   !ks.chunk ? 0 : ks.kind == Kind::Cuckoo ? 16 : 1);
   bht_table* mt = const_cast<bht_table*>(t);
   if (t->timing) HIP_TRY(hipEventRecord(t->ev[2], st));
   if (ks.kind == Kind::Cuckoo) {
@@ -1707,9 +1747,13 @@ bht_status find64_enqueue(const bht_table* t, const uint64_t* q, uint64_t n, uin
   g.probes = probes;
   g.H = make_hash64(t->params, t->m, t->params.num_hashes);
   hipStream_t st = as_stream(stream);
-  const void* kernel = probes ? (const void*)wide_find_chunk_kernel<8, true>
-                              : (const void*)wide_find_chunk_kernel<8, false>;
-  const int grid = grid_for(kernel, n, t->grid_blocks, 16);
+  // a wave per 64 queries, as wave_find
+  const bool lanes = n <= kLaneFindQueries && !t->grid_blocks;
+  const void* kernel = lanes ? (probes ? (const void*)wide_find_lane_kernel<true>
+                                       : (const void*)wide_find_lane_kernel<false>)
+                             : (probes ? (const void*)wide_find_chunk_kernel<8, true>
+                                       : (const void*)wide_find_chunk_kernel<8, false>);
+  const int grid = lanes ? (int)((n + kBlock - 1) / kBlock) : grid_for(kernel, n, t->grid_blocks, 1);
   bht_table* mt = const_cast<bht_table*>(t);
   if (t->timing) HIP_TRY(hipEventRecord(t->ev[2], st));
   reinterpret_cast<void (*)(WideFindArgs)>(const_cast<void*>(kernel)) <<<grid, kBlock, 0, st>>>(g);
@@ -1760,6 +1804,7 @@ bht_status bht_set_tuning(bht_table* t, const bht_tuning* tuning) {
   t->build_mode = tuning->build_mode;
   t->iht_early_exit = tuning->iht_early_exit;
   t->unroll = tuning->query_unroll ? tuning->query_unroll : default_unroll(t->scheme, t->b);
+  t->unroll_set = tuning->query_unroll != 0;
   return BHT_OK;
 }
 
@@ -1921,13 +1966,18 @@ bht_status bht_batch_create(const bht_batch_entry* entries, uint32_t count, uint
         (e.n_queries && (!e.d_queries || !e.d_out_values || !e.d_out_found)))
       return fail(BHT_ERR_INVALID_ARG, "null data pointer in batch");
   }
+  // one query per lane unless a caller asked for two (256 tables, 12 M
+  // queries: 230 us against 255)
+  uint32_t unroll = 1;
+  for (uint32_t i = 0; i < count; ++i)
+    if (entries[i].table->unroll_set) unroll = t0->unroll;
   const void* bk = nullptr;
   const void* fk = nullptr;
 #define BHT_BATCH_CASE(B_, W_)                                             \
   if (t0->b == B_ && t0->tile == W_) {                                     \
     bk = (const void*)batch_build_kernel<B_, W_>;                          \
-    fk = t0->unroll == 2 ? (const void*)batch_find_kernel<B_, W_, 2>       \
-                         : (const void*)batch_find_kernel<B_, W_, 1>;      \
+    fk = unroll == 2 ? (const void*)batch_find_kernel<B_, W_, 2>           \
+                     : (const void*)batch_find_kernel<B_, W_, 1>;          \
   }
   BHT_BATCH_CASE(8, 4)
   BHT_BATCH_CASE(8, 8)
@@ -1961,7 +2011,7 @@ bht_status bht_batch_create(const bht_batch_entry* entries, uint32_t count, uint
   uint64_t total_q = 0;
   for (uint32_t i = 0; i < count; ++i) total_q += entries[i].n_queries;
   const uint32_t find_size =
-      open_size ? find_item_size(fk, total_q, t0->unroll == 2 ? 128 : 64) : item_size;
+      open_size ? find_item_size(fk, total_q, 64 * unroll) : item_size;
   std::vector<BatchTable> tables(count);
   std::vector<BatchItem> fill, build, find;
   const uint64_t fill_words = 1ull << 16;

@@ -776,6 +776,84 @@ __global__ __launch_bounds__(kBlock) void cuckoo_find_chunk_kernel(FindArgs32 g)
   cuckoo_find_chunk_range<B, W, COUNT, Q>(g, wave_range(g.n));
 }
 
+// Same query, a wave answers one chunk of 64 queries and ends, and the
+// dispatcher keeps the device full: waves that loop over a longer range
+// finish at different times (a chunk takes one to three dependent reads),
+// and a launch of few chunks per wave rounds up.  Chunk kernel with two
+// queries per lane over resident waves, and this one, us (half the queries
+// absent, LF 0.9): 2^20 queries on 2^20 pairs 29.6 and 25.8, on 2^24 pairs
+// 37.8 and 35.4; 2^22 on 2^20 94 and 76, on 2^24 129 and 120; 2^26 on 2^26
+// 1807 and 1770.
+template <int B, int W, bool COUNT>
+__global__ __launch_bounds__(kBlock) void cuckoo_find_wave_kernel(FindArgs32 g) {
+  const uint32_t lane = __lane_id();
+  const uint32_t tb = lane & ~(uint32_t)(W - 1);
+  const uint32_t lt = lane & (uint32_t)(W - 1);
+  const uint64_t idx = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
+  const bool valid = idx < g.n;
+  const uint32_t q = valid ? g.queries[idx] : kEmptyKey;
+  bool open = q != kEmptyKey;
+  uint32_t out = kEmptyKey, rounds = 0;
+  uint8_t found = 0;
+  for (uint32_t round = 0; round < g.H.h; ++round) {
+    const uint64_t om = ballot(open);
+    if (om == 0) break;
+    const uint32_t bucket = open ? hash32_dyn(g.H, round, q) : 0u;
+    Part<B / W> d[W];
+    tile_read<B, W>(g.slots, bucket, om, tb, lt, d);
+    bool hit = false, room = false;
+    uint32_t value = kEmptyKey;
+    tile_match<B, W>(d, q, tb, lt, &hit, &room, &value);
+    if (open) {
+      rounds = round + 1;
+      if (hit) {
+        out = value;
+        found = 1;
+      }
+      open = !hit && !room;
+    }
+  }
+  if (valid) {
+    g.out_v[idx] = out;
+    g.out_f[idx] = found;
+    if (COUNT) g.probes[idx] = (uint8_t)rounds;
+  }
+}
+
+// Same query for launches that leave the device idle, where the length of
+// one wave's instruction stream counts: every lane reads its own bucket
+// whole (8 loads and 48 compares for 16 slots, a third of the instructions
+// of the tile read and match).  256 queries 6.3 us against 7.2 (8.5 with two
+// per lane), 2^17 8.1 against 8.7; from 2^18 the tile read is faster, since
+// a lane's loads take the L1 64 cycles each (2^22 on 2^20 pairs: 105 us).
+template <int B, bool COUNT>
+__global__ __launch_bounds__(kBlock) void cuckoo_find_lane_kernel(FindArgs32 g) {
+  const uint64_t idx = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (idx >= g.n) return;
+  const uint32_t q = g.queries[idx];
+  bool open = q != kEmptyKey;
+  uint32_t out = kEmptyKey, round = 0;
+  uint8_t found = 0;
+  for (; open && round < g.H.h; ++round) {
+    const uint64_t* p = g.slots + (uint64_t)hash32_dyn(g.H, round, q) * B;
+    const Part<B> d = load_part<B>(p);
+    uint32_t most = 0;                     // the empty key, if some slot is empty
+#pragma unroll
+    for (int i = 0; i < B; ++i) {
+      const uint32_t k = (uint32_t)d.s[i];
+      most = most > k ? most : k;
+      if (k == q) {
+        out = (uint32_t)(d.s[i] >> 32);
+        found = 1;
+      }
+    }
+    open = !found && most != kEmptyKey;
+  }
+  g.out_v[idx] = out;
+  g.out_f[idx] = found;
+  if (COUNT) g.probes[idx] = (uint8_t)round;
+}
+
 // Parallel probing (the alternative noted in Section II-A): all h candidate
 // buckets of a query are read at once, so a query costs one memory latency
 // instead of up to h dependent ones, at h probes per query.  A stored key

@@ -509,4 +509,38 @@ __global__ __launch_bounds__(kBlock) void wide_find_chunk_kernel(WideFindArgs g)
   }
 }
 
+// Same query for launches that leave the device idle, as
+// cuckoo_find_lane_kernel: every lane reads its own bucket whole.
+template <bool COUNT>
+__global__ __launch_bounds__(kBlock) void wide_find_lane_kernel(WideFindArgs g) {
+  constexpr int B = 8;
+  const uint64_t idx = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (idx >= g.n) return;
+  const uint64_t q = g.queries[idx];
+  bool open = q < kBusy64;
+  uint64_t out = kEmpty64;
+  uint8_t found = 0;
+  uint32_t round = 0;
+  for (; open && round < g.H.h; ++round) {
+    const u64x2* p = reinterpret_cast<const u64x2*>(g.slots) +
+                     hash64(sel4(g.H.a, round), sel4(g.H.c, round), q, g.H.M, g.H.m) * B;
+    u64x2 d[B];
+#pragma unroll
+    for (int i = 0; i < B; ++i) d[i] = p[i];
+    bool room = false;
+#pragma unroll
+    for (int i = 0; i < B; ++i) {
+      room |= d[i].x == kEmpty64;
+      if (d[i].x == q) {
+        out = d[i].y;
+        found = 1;
+      }
+    }
+    open = !found && !room;
+  }
+  g.out_v[idx] = out;
+  g.out_f[idx] = found;
+  if (COUNT) g.probes[idx] = (uint8_t)round;
+}
+
 }  // namespace bht

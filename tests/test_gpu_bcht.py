@@ -408,3 +408,54 @@ def test_builds_from_several_threads_and_streams():
     for th in threads:
         th.join()
     assert not wrong
+
+
+@pytest.mark.parametrize("scheme,b,tile", [("bcht", 16, None), ("bcht", 16, 8), ("bcht", 4, None),
+                                           ("bcht", 8, 4), ("bcht", 32, None), ("cht1", 1, None),
+                                           ("wide", 8, None)])
+def test_find_around_the_wave_kernels_sizes(scheme, b, tile):
+    """Default queries around one chunk, one block and the size (2^17) from
+    which lanes share their bucket reads: values and flags equal brute force
+    and probe counts the oracle's, reserved keys among the queries included,
+    and outputs past the last query are left alone."""
+    import torch
+    B = bht()
+    wide, n = scheme == "wide", 20000
+    kind = "bcht" if wide else scheme
+    keys = datagen.unique_keys64(n, 97) if wide else datagen.unique_keys(n, 97)
+    vals = datagen.values64(n, 97) if wide else datagen.values(n, 97)
+    for s in range(10):
+        p = oracle.params_for(kind, n, 0.8, 9700 + s, b=b, wide=wide)
+        t = B.Table(p.m * b, b, kind, p.a, p.c, key_bits=64 if wide else 32, rng_seed=p.rng_seed,
+                    tile=tile)
+        if t.build(dev(keys), dev(vals)) == B.BHT_OK:
+            break
+        t.close()
+    else:
+        pytest.fail("no build succeeded")
+    layout = t.download()
+    big = (1 << 17) + 70
+    q = datagen.mixed_queries(n, big, 0.6, 97, wide=wide)
+    q[5] = q[70] = np.iinfo(q.dtype).max
+    bv, bf = (oracle.brute_find64 if wide else oracle.brute_find32)(keys, vals, q)
+    per = (oracle.find64 if wide else oracle.find32)(p, layout, q)[3]
+    for m in (1, 63, 64, 65, 255, 256, 257, 1 << 17, (1 << 17) + 1, big):
+        ov = torch.full((m + 64,), 77, dtype=torch.int64 if wide else torch.int32, device="cuda")
+        of = torch.full((m + 64,), 7, dtype=torch.uint8, device="cuda")
+        pr = torch.full((m + 64,), 9, dtype=torch.uint8, device="cuda")
+        dq = dev(q[:m])
+        for counted in (False, True):
+            ov.fill_(77)
+            of.fill_(7)
+            if counted:
+                (B.bht_find64_counted if wide else B.bht_find_counted)(t.handle, dq, ov, of, pr, n=m)
+            else:
+                (B.bht_find64 if wide else B.bht_find)(t.handle, dq, ov, of, n=m)
+            torch.cuda.synchronize()
+            got = ov[:m].cpu().numpy()
+            np.testing.assert_array_equal(got.view(bv.dtype), bv[:m])
+            np.testing.assert_array_equal(host_u8(of[:m]), bf[:m])
+            assert bool((ov[m:] == 77).all()) and bool((of[m:] == 7).all())
+        np.testing.assert_array_equal(host_u8(pr[:m]), per[:m])
+        assert bool((pr[m:] == 9).all())
+    t.close()
