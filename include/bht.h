@@ -302,8 +302,9 @@ bht_status bht_get_probe_stats(const bht_table* t, uint64_t* build_probes, uint6
  * inserted at their secondary choices afterwards, concurrently (a pair
  * reaches the secondary level only once its primary holds iht_threshold
  * pairs, as the threshold rule requires).  BHT_BUILD_AUTO partitions builds of at least 2^15 pairs
- * (2^17 with fewer than 8 slots per bucket, 2^18
- * for two-level iceberg tables, never one-level ones) into
+ * (2^17 with fewer than 8 slots per bucket, 2^18 for
+ * two-level iceberg tables, 2^10 if their primaries fill whole
+ * (iht_threshold = bucket_size), never for one-level ones) into
  * tables whose memory the library owns (bht_create); below 2^18 pairs only
  * where the workspace is allocated or can be (not while the stream is
  * captured).

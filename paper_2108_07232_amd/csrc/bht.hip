@@ -532,12 +532,35 @@ const void* wave_find(const bht_table* t, uint64_t n, bool count) {
   return count ? wave_find_t<true>(t, n) : wave_find_t<false>(t, n);
 }
 
+// Power-of-two builds of up to this many pairs take the counted kernel, with
+// at most kP2Lanes pairs under way (at LF 0.8, us, bucket-reading and counted
+// kernel: 5,000 pairs 217 and 22, 100,003 306 and 40, 2^20 328 and 90, 2^22
+// 392 and 268, 2^23 615 and 528; past that its two loads and an atomic beside
+// the stored pair leave the last-level cache: 2^24 1288 and 1306, 2^26 5684
+// and 6951.  2^20 pairs with 48, 64, 96, 128, 256 K lanes: 98, 90, 92, 96,
+// 134).
+constexpr uint64_t kP2CountMaxKeys = 1ull << 23;
+constexpr uint64_t kP2Lanes = 1ull << 16;
+
+// The same for the secondary step of two-level iceberg builds (whole build at
+// LF 0.8, us, bucket-reading and counted: 2^18 pairs 144 and 43, 10^6 122 and
+// 68, 3,000,017 123 and 87, 2^23 269 and 240, 2^24 418 and 386, 2^26 1190 and
+// 1249).
+constexpr uint64_t kIcebergCountMaxKeys = 1ull << 24;
+
+// Bytes of the counts of n pairs' build (0: secondaries are read).
+uint64_t iceberg_count_bytes(const bht_table* t, uint64_t n) {
+  if (t->scheme != BHT_IHT || !t->params.iht_secondary_b || n > kIcebergCountMaxKeys) return 0;
+  return t->params.iht_secondary_m * p2_count_stride(t->params.iht_secondary_b) * 4;
+}
+
 struct PartKernels {
   const void* place;
   const void* place_mid;       // bins of at most 2 * kSmallBinSlots slots
   const void* place_small;     // bins of at most kSmallBinSlots slots
   const void* overflow;
   const void* overflow_both;   // the overflow insertion of small builds (cuckoo)
+                               // or with secondary counts (two-level iceberg)
   bool iceberg;          // placement without eviction, iceberg overflow insertion
 };
 
@@ -547,19 +570,21 @@ bool part_kernels(const bht_table* t, uint32_t w, PartKernels* k) {
   const uint32_t b = t->b;
   if (t->scheme == BHT_IHT) {
     const uint32_t b2 = t->params.iht_secondary_b;
-#define BHT_ICASE(B_, B2_, W_)                                                     \
+#define BHT_COMMA ,
+#define BHT_ICASE(B_, B2_, W_, BOTH_)                                              \
   if (b == B_ && b2 == B2_ && w == W_) {                                           \
     *k = {(const void*)bin_place_kernel<B_, false, bin_slots<B_>()>,               \
           (const void*)bin_place_kernel<B_, false, 2 * kSmallBinSlots>,            \
           (const void*)bin_place_kernel<B_, false, kSmallBinSlots>,                \
-          (const void*)iceberg_overflow_kernel<B_, B2_, W_>, nullptr, true};       \
+          (const void*)iceberg_overflow_kernel<B_, B2_, W_>, BOTH_, true};         \
     return true;                                                                   \
   }
-    BHT_ICASE(16, 0, 8)
-    BHT_ICASE(16, 8, 8)
-    BHT_ICASE(32, 0, 16)
-    BHT_ICASE(32, 8, 16)
+    BHT_ICASE(16, 0, 8, nullptr)
+    BHT_ICASE(16, 8, 8, (const void*)iceberg_count_overflow_kernel<16 BHT_COMMA 8>)
+    BHT_ICASE(32, 0, 16, nullptr)
+    BHT_ICASE(32, 8, 16, (const void*)iceberg_count_overflow_kernel<32 BHT_COMMA 8>)
 #undef BHT_ICASE
+#undef BHT_COMMA
     return false;
   }
   if (t->scheme != BHT_BCHT && t->scheme != BHT_CHT1) return false;
@@ -744,16 +769,32 @@ bool use_partitioned(const bht_table* t, uint64_t n, bool counting) {
 
 char* table_workspace(bht_table* t, uint64_t bytes, hipStream_t st);
 
-// Whether a cuckoo build below kPartWorkspaceKeys takes the partitioned path
+// Two-level iceberg builds from this many pairs on (LF 0.8, us, concurrent
+// and partitioned with counted secondaries: 20,000 pairs 239 and 45, 40,000
+// 267 and 35, 100,003 265 and 37, 200,000 273 and 40), where primaries fill
+// whole (t = b).  With t < b the pairs whose secondaries are full return to
+// their primary, and there the serial order matters: a bucket with many pairs
+// sends its first ones on early, while secondaries have room (30,001 pairs at
+// LF 0.75 with t = 12 build for 7 of 10 constant sets in input order and for
+// none after all primaries).
+constexpr uint64_t kIcebergSmallKeys = 1ull << 10;
+
+// Whether a build below kPartWorkspaceKeys takes the partitioned path
 // (64-bit pairs, concurrent and partitioned build at LF 0.9, us: 20,000 pairs
 // 83 and 83, 50,000 94 and 67, 100,003 101 and 73, 200,000 121 and 85).
 bool use_small_partitioned(bht_table* t, uint64_t n, bool counting, hipStream_t st) {
-  if (counting || n < part_min_keys(t->b) || n >= kPartWorkspaceKeys) return false;
-  if (t->scheme != BHT_BCHT && t->scheme != BHT_CHT1) return false;
+  if (counting || n >= kPartWorkspaceKeys) return false;
+  if (t->scheme == BHT_IHT) {
+    if (!t->params.iht_secondary_b || t->params.iht_threshold < t->b || n < kIcebergSmallKeys)
+      return false;
+  } else if ((t->scheme != BHT_BCHT && t->scheme != BHT_CHT1) || n < part_min_keys(t->b)) {
+    return false;
+  }
   if (t->build_mode != BHT_BUILD_AUTO || !t->owns_memory) return false;
   PartPlan P;
   if (!part_plan(t, n, &P)) return false;
-  return table_workspace(t, part_layout(P, n, t->key_bits / 8).bytes, st) != nullptr;
+  return table_workspace(t, part_layout(P, n, t->key_bits / 8).bytes + iceberg_count_bytes(t, n),
+                         st) != nullptr;
 }
 
 // The one-workgroup build of a table that fits LDS, or null: the default of
@@ -940,7 +981,12 @@ bht_status build32_partitioned(bht_table* t, const uint32_t* keys, const uint32_
   PartKernels K;
   if (!part_kernels(t, t->tile, &K))
     return fail(BHT_ERR_UNSUPPORTED, "no kernel for this bucket size and tile width");
-  const PartLayout L = part_layout(P, n);
+  PartLayout L = part_layout(P, n);
+  // counts of the secondary buckets, in the table's own workspace
+  const bool counted = !ws && iceberg_count_bytes(t, n) != 0;
+  const uint64_t m2 = t->params.iht_secondary_m;
+  const uint64_t counts_at = L.bytes;
+  if (counted) L.bytes += iceberg_count_bytes(t, n);
   char* w = nullptr;
   bht_status ws_status = part_workspace(t, L, st, ws, ws_bytes, &w);
   if (ws_status != BHT_OK) return ws_status;
@@ -998,9 +1044,17 @@ bht_status build32_partitioned(bht_table* t, const uint32_t* keys, const uint32_
     // builds at 0.86 and needed a spread of 32).
     const uint64_t sec_buckets = t->params.iht_secondary_b ? t->params.iht_secondary_m : t->m;
     const uint64_t lanes = std::max<uint64_t>(sec_buckets / kIcebergOverflowSpread, 64);
-    const int ig = grid_for(K.overflow, lanes, t->grid_blocks);
+    const void* kernel = counted ? K.overflow_both : K.overflow;
+    int ig = grid_for(kernel, lanes, t->grid_blocks);
+    if (counted) {
+      ig = grid_for(kernel, kP2Lanes, t->grid_blocks);
+      ia.counts = reinterpret_cast<uint32_t*>(w + counts_at);
+      const int clear_grid = (int)std::min<uint64_t>((m2 + kBlock - 1) / kBlock, 4096);
+      p2_clear_kernel<<<clear_grid, kBlock, 0, st>>>(ia.counts, m2,
+                                                     p2_count_stride(t->params.iht_secondary_b));
+    }
     ia.parts = overflow_parts(ig, P.nbins);
-    reinterpret_cast<void (*)(IcebergOverflowArgs)>(const_cast<void*>(K.overflow))
+    reinterpret_cast<void (*)(IcebergOverflowArgs)>(const_cast<void*>(kernel))
         <<<ig, kBlock, 0, st>>>(ia);
   } else {
     OverflowArgs oa;
@@ -1030,16 +1084,6 @@ bht_status build32_partitioned(bht_table* t, const uint32_t* keys, const uint32_
   t->pending_partitioned = true;
   return BHT_OK;
 }
-
-// Power-of-two builds of up to this many pairs take the counted kernel, with
-// at most kP2Lanes pairs under way (at LF 0.8, us, bucket-reading and counted
-// kernel: 5,000 pairs 217 and 22, 100,003 306 and 40, 2^20 328 and 90, 2^22
-// 392 and 268, 2^23 615 and 528; past that its two loads and an atomic beside
-// the stored pair leave the last-level cache: 2^24 1288 and 1306, 2^26 5684
-// and 6951.  2^20 pairs with 48, 64, 96, 128, 256 K lanes: 98, 90, 92, 96,
-// 134).
-constexpr uint64_t kP2CountMaxKeys = 1ull << 23;
-constexpr uint64_t kP2Lanes = 1ull << 16;
 
 // The counted power-of-two build of n pairs into table t, or null.
 const void* p2_count_kernel(const bht_table* t, uint64_t n, bool counting) {

@@ -374,3 +374,48 @@ def test_power_of_two_counted_build(b, lf, n):
     if B.bht_build_wait(t.handle) == B.BHT_OK:
         assert oracle.check32(p, t.download(), keys, vals)[0] == 0
     t.close()
+
+
+@pytest.mark.parametrize("b,thr,lf,n", [(16, 16, 0.8, 1023), (16, 16, 0.8, 1024), (16, 12, 0.75, 30001),
+                                        (32, 32, 0.8, 100003), (32, 20, 0.6, 262144),
+                                        (16, 16, 0.8, (1 << 24) + 1)])
+def test_iceberg_counted_secondaries(b, thr, lf, n):
+    """Default two-level builds around the sizes where the partitioned path
+    and its secondary counts begin and end, with thresholds that leave room in
+    the primary for pairs whose secondaries are full: valid layout (threshold
+    rule included), exact lookups, exact count of pairs sent on; a captured
+    first build, which has no workspace, builds as well."""
+    import torch
+    B = bht()
+    keys, vals = workload(n, 89)
+    dk, dv = dev(keys), dev(vals)
+    for s in range(10):
+        p = iceberg_params(n, lf, 8900 + s, b=b, b2=8, threshold=thr)
+        t = gpu_table(p)
+        if t.build(dk, dv) == B.BHT_OK:
+            break
+        t.close()
+    else:
+        pytest.fail("no build succeeded")
+    assert oracle.check32(p, t.download(), keys, vals)[0] == 0
+    check_find(t, p, keys, vals, datagen.mixed_queries(n, min(2 * n, 1 << 20), 0.5, 89))
+    part, sent, probes = B.bht_build_stats(t.handle)
+    # below 2^18 pairs only where primaries fill whole
+    assert part == (n >= 1 << 18 or (n >= 1024 and thr == b))
+    if part:
+        h0 = oracle.hash32_many(p.a[0], p.c[0], keys, p.m)
+        counts = np.bincount(h0.astype(np.int64), minlength=p.m)
+        assert sent == int(np.maximum(counts - thr, 0).sum()) and probes >= 2 * sent
+    t.close()
+    if n >= 1 << 18:
+        return
+    t = gpu_table(p)
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        B.bht_build_async(t.handle, dk, dv, stream=side)
+    for _ in range(2):
+        graph.replay()
+        torch.cuda.synchronize()
+    if B.bht_build_wait(t.handle) == B.BHT_OK:
+        assert oracle.check32(p, t.download(), keys, vals)[0] == 0
+    t.close()
