@@ -2389,10 +2389,12 @@ bht_status bht_multi_find(bht_find_ctx* c, const bht_find_request* reqs, uint32_
     return fail(BHT_ERR_CAPACITY, "more work items than the context holds");
   const void* fk = nullptr;
   const void* ik = nullptr;
+  const void* lk = nullptr;
 #define BHT_MF_CASE(B_, W_)                              \
   if (t0->b == B_ && t0->tile == W_) {                   \
     fk = (const void*)batch_find_kernel<B_, W_>;         \
     ik = (const void*)inline_find_kernel<B_, W_>;        \
+    lk = (const void*)inline_find_lane_kernel<B_>;       \
   }
   BHT_MF_CASE(8, 4)
   BHT_MF_CASE(8, 8)
@@ -2408,9 +2410,14 @@ bht_status bht_multi_find(bht_find_ctx* c, const bht_find_request* reqs, uint32_
     // to one 64-query chunk) until every wave has about one item.
     uint64_t total_q = 0;
     for (uint32_t i = 0; i < count; ++i) total_q += reqs[i].n;
-    const uint64_t waves = (uint64_t)grid_for(ik, 1ull << 40) * (kBlock / 64);
-    const uint64_t even = ((total_q + waves - 1) / waves + 63) / 64 * 64;
-    item_size = (uint32_t)std::max<uint64_t>(64, std::min<uint64_t>(item_size, even));
+    const bool lanes = total_q <= kLaneFindQueries;
+    if (lanes) {
+      item_size = 64;
+    } else {
+      const uint64_t waves = (uint64_t)grid_for(ik, 1ull << 40) * (kBlock / 64);
+      const uint64_t even = ((total_q + waves - 1) / waves + 63) / 64 * 64;
+      item_size = (uint32_t)std::max<uint64_t>(64, std::min<uint64_t>(item_size, even));
+    }
     InlineFind arg;
     memset(&arg, 0, sizeof(arg));
     uint32_t first = 0;
@@ -2430,8 +2437,9 @@ bht_status bht_multi_find(bht_find_ctx* c, const bht_find_request* reqs, uint32_
     arg.count = count;
     arg.item_size = item_size;
     if (first == 0) return BHT_OK;
-    const int grid = grid_for(ik, (uint64_t)first * kBlock);
-    reinterpret_cast<void (*)(InlineFind)>(const_cast<void*>(ik))
+    const int grid = lanes ? (int)((first + kBlock / 64 - 1) / (kBlock / 64))
+                           : grid_for(ik, (uint64_t)first * kBlock);
+    reinterpret_cast<void (*)(InlineFind)>(const_cast<void*>(lanes ? lk : ik))
         <<<grid, kBlock, 0, as_stream(stream)>>>(arg);
     HIP_TRY(hipGetLastError());
     return BHT_OK;

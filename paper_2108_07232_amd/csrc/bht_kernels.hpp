@@ -827,9 +827,7 @@ __global__ __launch_bounds__(kBlock) void cuckoo_find_wave_kernel(FindArgs32 g) 
 // per lane), 2^17 8.1 against 8.7; from 2^18 the tile read is faster, since
 // a lane's loads take the L1 64 cycles each (2^22 on 2^20 pairs: 105 us).
 template <int B, bool COUNT>
-__global__ __launch_bounds__(kBlock) void cuckoo_find_lane_kernel(FindArgs32 g) {
-  const uint64_t idx = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (idx >= g.n) return;
+__device__ __forceinline__ void cuckoo_find_lane(const FindArgs32& g, uint64_t idx) {
   const uint32_t q = g.queries[idx];
   bool open = q != kEmptyKey;
   uint32_t out = kEmptyKey, round = 0;
@@ -852,6 +850,12 @@ __global__ __launch_bounds__(kBlock) void cuckoo_find_lane_kernel(FindArgs32 g) 
   g.out_v[idx] = out;
   g.out_f[idx] = found;
   if (COUNT) g.probes[idx] = (uint8_t)round;
+}
+
+template <int B, bool COUNT>
+__global__ __launch_bounds__(kBlock) void cuckoo_find_lane_kernel(FindArgs32 g) {
+  const uint64_t idx = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (idx < g.n) cuckoo_find_lane<B, COUNT>(g, idx);
 }
 
 // Parallel probing (the alternative noted in Section II-A): all h candidate

@@ -7,7 +7,7 @@ import pytest
 import datagen
 import oracle
 from datagen import workloads
-from tests._util import host_u32, host_u8
+from tests._util import dev, host_u32, host_u8
 
 pytestmark = pytest.mark.gpu
 
@@ -90,3 +90,29 @@ def test_budget_evicts_least_recently_used_never_in_use():
         if r.kind == "lookup" and r.status != bht.BHT_OK:
             assert r.status == bht.BHT_ERR_NOT_BUILT
     srv.close()
+
+
+@pytest.mark.parametrize("sizes", [[1], [64, 65, 63, 1, 200], [1 << 16, (1 << 16) - 1, 1],
+                                   [1 << 16, 1 << 16, 1], [300000, 5, 128]])
+def test_few_requests_around_the_per_lane_size(sizes):
+    """Requests whose queries together stay below, reach and exceed the number
+    (2^17) up to which a coalesced launch reads buckets per lane: each equals
+    the same lookup made alone."""
+    import torch
+    import paper_2108_07232_amd as bht
+    n = 30000
+    keys, vals = datagen.unique_keys(n, 99), datagen.values(n, 99)
+    p = oracle.params_for("bcht", n, 0.85, 99)
+    t = bht.Table(p.m * p.b, p.b, "bcht", p.a, p.c, rng_seed=p.rng_seed)
+    assert t.build(dev(keys), dev(vals)) == bht.BHT_OK
+    ctx = bht.bht_find_ctx_create(8, 4096)
+    q = [dev(datagen.mixed_queries(n, m, 0.5, 100 + i)) for i, m in enumerate(sizes)]
+    outs = [(torch.full((m,), 3, dtype=torch.int32, device="cuda"),
+             torch.full((m,), 3, dtype=torch.uint8, device="cuda")) for m in sizes]
+    bht.bht_multi_find(ctx, [(t.handle, a, o[0], o[1]) for a, o in zip(q, outs)])
+    for a, o in zip(q, outs):
+        v, f = t.find(a)
+        assert torch.equal(v, o[0]) and torch.equal(f, o[1])
+    torch.cuda.synchronize()
+    bht.bht_find_ctx_destroy(ctx)
+    t.close()
