@@ -202,7 +202,10 @@ uint32_t overflow_parts(uint64_t blocks, uint64_t nbins) {
 // most 4 blocks per CU.  A phase that fills the device is bound by the slot
 // atomics, and more lanes in flight only make them slower (2^27 pairs, LF
 // 0.9: 649, 590, 585, 592, 604 us at 2 to 6 blocks per CU).
-int overflow_grid(const void* kernel, uint64_t items) {
+// `fixed` (0: none) is the caller's choice, up to what the counts of blocks
+// that share a stat line hold.
+int overflow_grid(const void* kernel, uint64_t items, uint32_t fixed = 0) {
+  if (fixed) return (int)std::min(fixed, 1u << 20);
   static std::mutex mu;
   static std::map<int, int> known;
   int dev = 0, cus = 0;
@@ -324,13 +327,12 @@ bool valid_params(const bht_params& p, bht_scheme scheme, uint32_t b, std::strin
 // Lanes per bucket read.  Every lane owns one operation whatever the width;
 // the width only splits each bucket read among a tile's lanes.  A cuckoo
 // table of 16-slot buckets takes 4 lanes of 32 bytes (two 16-byte loads per
-// bucket per lane): its query and overflow kernels need 70 registers per
-// lane instead of 82 and keep 7 waves per SIMD instead of 5, measured 0.3%
-// faster in the queries and 2.5% in the overflow insertion (2 lanes: queries
-// 1.5% slower; 1 lane: 9% slower).  The other schemes keep one 16-byte load
-// per lane.
-// Queries per lane per chunk of the chunk schedule.  Cuckoo tables of
-// 16-slot buckets (4-lane tiles) take 2: measured 0.7% faster queries.
+// bucket per lane): its query kernels need fewer registers per lane than with
+// 8, measured 0.3% faster (2 lanes: queries 1.5% slower; 1 lane: 9% slower).
+// The other schemes keep one 16-byte load per lane.
+// Queries per lane per chunk of the chunk schedule when it is asked for.
+// Cuckoo tables of 16-slot buckets (4-lane tiles) take 2: measured 0.7%
+// faster than 1 there.
 uint32_t default_unroll(bht_scheme scheme, uint32_t b) {
   return (scheme == BHT_BCHT || scheme == BHT_CHT1) && b == 16 ? 2 : 1;
 }
@@ -960,8 +962,8 @@ bht_status build64_partitioned(bht_table* t, const uint64_t* keys, const uint64_
   void (*const overflow)(WideOverflowArgs) =
       both ? wide_overflow_kernel<true> : wide_overflow_kernel<false>;
   oa.parts = overflow_parts(overflow_grid((const void*)overflow, ~0ull), P.nbins);
-  const int og = t->grid_blocks ? (int)t->grid_blocks
-                                : overflow_grid((const void*)overflow, (uint64_t)P.nbins * oa.parts);
+  const int og =
+      overflow_grid((const void*)overflow, (uint64_t)P.nbins * oa.parts, t->grid_blocks);
   overflow<<<og, kBlock, 0, st>>>(oa);
   HIP_TRY(hipGetLastError());
   if (t->timing) HIP_TRY(hipEventRecord(t->ev[1], st));
@@ -1045,9 +1047,9 @@ bht_status build32_partitioned(bht_table* t, const uint32_t* keys, const uint32_
     const uint64_t sec_buckets = t->params.iht_secondary_b ? t->params.iht_secondary_m : t->m;
     const uint64_t lanes = std::max<uint64_t>(sec_buckets / kIcebergOverflowSpread, 64);
     const void* kernel = counted ? K.overflow_both : K.overflow;
-    int ig = grid_for(kernel, lanes, t->grid_blocks);
+    int ig = std::min(grid_for(kernel, lanes, t->grid_blocks), 1 << 20);
     if (counted) {
-      ig = grid_for(kernel, kP2Lanes, t->grid_blocks);
+      ig = std::min(grid_for(kernel, kP2Lanes, t->grid_blocks), 1 << 20);
       ia.counts = reinterpret_cast<uint32_t*>(w + counts_at);
       const int clear_grid = (int)std::min<uint64_t>((m2 + kBlock - 1) / kBlock, 4096);
       p2_clear_kernel<<<clear_grid, kBlock, 0, st>>>(ia.counts, m2,
@@ -1071,8 +1073,7 @@ bht_status build32_partitioned(bht_table* t, const uint32_t* keys, const uint32_
     oa.nbins = P.nbins;
     const void* kernel = small_overflow(K.overflow, P.nbins) ? K.overflow_both : K.overflow;
     oa.parts = overflow_parts(overflow_grid(kernel, ~0ull), P.nbins);
-    const int og = t->grid_blocks ? (int)t->grid_blocks
-                                  : overflow_grid(kernel, (uint64_t)P.nbins * oa.parts);
+    const int og = overflow_grid(kernel, (uint64_t)P.nbins * oa.parts, t->grid_blocks);
     reinterpret_cast<void (*)(OverflowArgs)>(const_cast<void*>(kernel))
         <<<og, kBlock, 0, st>>>(oa);
   }

@@ -26,8 +26,9 @@
 //      first cuckoo step), and the evicted pair is kept, in place at the
 //      front of the bin's input range; the whole bin, empty slots included,
 //      is written to the table with full-line stores (so no reset pass);
-//   3. overflow: the concurrent cuckoo insertion continues every evicted
-//      pair at its next bucket, bin by bin from a device work queue.
+//   3. overflow: every evicted pair goes on to the first of its next two
+//      buckets with room, or evicts again there, concurrently, bins (or
+//      parts of bins) taken from device work queues.
 //
 // Steps 2 and 3 are Section III-A's insertion under a deferred-victim
 // schedule: every pair first claims a slot of its first bucket (at slot =

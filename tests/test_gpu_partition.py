@@ -393,3 +393,24 @@ def test_default_build_around_its_thresholds(b, n, lf):
     assert not B.bht_build_stats(t.handle)[0]
     check_table(t, params, keys, vals)
     t.close()
+
+
+@pytest.mark.parametrize("grid", [1, 3, 17, 70000])
+def test_overflow_queues_with_a_given_grid(grid):
+    """The overflow phase with fewer blocks than queue heads, with more items
+    than waves, and with far more blocks than items: every evicted pair is
+    inserted once and counted once."""
+    B = bht()
+    n = 300007
+    keys, vals = workload(n, 88)
+    params = oracle.params_for("bcht", n, 0.9, 8800)
+    t = B.Table(params.m * 16, 16, "bcht", params.a, params.c, rng_seed=params.rng_seed,
+                grid_blocks=grid)
+    assert t.build(dev(keys), dev(vals)) == B.BHT_OK
+    check_table(t, params, keys, vals)
+    h0 = oracle.hash32_many(params.a[0], params.c[0], keys, params.m)
+    counts = np.bincount(h0.astype(np.int64), minlength=params.m)
+    part, evicted, probes = B.bht_build_stats(t.handle)
+    assert part and evicted == int(np.maximum(counts - 16, 0).sum())
+    assert evicted <= probes < 4 * evicted
+    t.close()
