@@ -391,7 +391,7 @@ bht_status bht_diag_stream(const void* d_src, void* d_dst, uint64_t bytes, uint6
  * their output arrays (all caller-owned device memory, as for bht_build and
  * bht_find).  bht_batch_create copies the table descriptors and the work
  * items (ranges of item_size pairs or queries; 0 = 8192 pairs, and queries
- * as many as spread over the device, at most 8192) to the device.
+ * as many as spread over the device, 64 to 8192) to the device.
  * bht_batch_run enqueues a reset of the batch's queues and statuses, the
  * build of every table and one persistent query kernel pulling (table,
  * range) items from a device-side queue.  The build is the partitioned

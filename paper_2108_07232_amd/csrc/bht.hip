@@ -365,14 +365,17 @@ constexpr uint32_t kDefaultSchedule = BHT_FIND_CHUNK;
 constexpr uint64_t kHeadBytes = kQueueHeads * kAtomicLine * 4;  // the heads of one queue
 
 // Queries per work item of a batch whose caller leaves the size open: about
-// 8 items per resident wave, in whole chunks of `chunk` queries, at most
-// 8,192.  Larger items leave waves idle at the end and small tables' items
-// without neighbours (256 tables, 12 M queries: 600 us at 8,192 per item,
-// 412, 320, 280, 247, 246 us at 1, 2, 4, 8, 16 items per wave).
+// 8 items per resident wave, so that waves do not wait for the last ones, and
+// at most 256 queries (2^20 items), so that the tables the waves are on at
+// one time stay in the last-level cache.  256 tables, 12 M queries: 600 us at
+// 8,192 per item, 412, 320, 280, 247, 246 us at 1, 2, 4, 8, 16 items per wave;
+// 1,024 tables, 515 M queries, whole run: 22.4, 21.8, 21.2, 20.0, 18.7 ms at
+// 8,192, 2,048, 1,024, 512, 256 per item.
 uint32_t find_item_size(const void* kernel, uint64_t queries, uint32_t chunk) {
   const uint64_t waves = (uint64_t)resident_blocks(kernel, kBlock) * (kBlock / 64);
   const uint64_t even = queries / (waves * 8) / chunk * chunk;
-  return (uint32_t)std::min<uint64_t>(std::max<uint64_t>(even, chunk), 8192);
+  const uint64_t most = std::min<uint64_t>(std::max<uint64_t>(256, (queries >> 20) / chunk * chunk), 8192);
+  return (uint32_t)std::min<uint64_t>(std::max<uint64_t>(even, chunk), most);
 }
 
 template <int B, int W, bool C>
@@ -2011,9 +2014,13 @@ bht_status bht_batch_create(const bht_batch_entry* entries, uint32_t count, uint
         (e.n_queries && (!e.d_queries || !e.d_out_values || !e.d_out_found)))
       return fail(BHT_ERR_INVALID_ARG, "null data pointer in batch");
   }
-  // one query per lane unless a caller asked for two (256 tables, 12 M
-  // queries: 230 us against 255)
-  uint32_t unroll = 1;
+  // Where no caller asked for an unroll, one query per lane in small batches
+  // (256 tables, 12 M queries: 230 us against 255), two in larger ones (512
+  // tables, 24 M queries and as many pairs built: 1.00 ms against 1.02; 1,024
+  // tables, 515 M: 18.7 against 19.7).
+  uint64_t total_q = 0;
+  for (uint32_t i = 0; i < count; ++i) total_q += entries[i].n_queries;
+  uint32_t unroll = total_q > (1ull << 24) ? t0->unroll : 1;
   for (uint32_t i = 0; i < count; ++i)
     if (entries[i].table->unroll_set) unroll = t0->unroll;
   const void* bk = nullptr;
@@ -2053,8 +2060,6 @@ bht_status bht_batch_create(const bht_batch_entry* entries, uint32_t count, uint
   BHT_BATCH_PCASE(32, 16)
 #undef BHT_BATCH_PCASE
 
-  uint64_t total_q = 0;
-  for (uint32_t i = 0; i < count; ++i) total_q += entries[i].n_queries;
   const uint32_t find_size =
       open_size ? find_item_size(fk, total_q, 64 * unroll) : item_size;
   std::vector<BatchTable> tables(count);
@@ -2107,8 +2112,12 @@ bht_status bht_batch_create(const bht_batch_entry* entries, uint32_t count, uint
     // of bin_slots / b buckets each), fewer than 2^32 pairs in all, and no
     // table asks for the concurrent build.
     // Tables of at most 1,024 small bins take those.
-    uint64_t most = 0;
-    for (uint32_t i = 0; i < count; ++i) most = std::max(most, entries[i].table->m);
+    uint64_t most = 0, pairs = 0;
+    for (uint32_t i = 0; i < count; ++i) {
+      most = std::max(most, entries[i].table->m);
+      pairs += entries[i].n_keys;
+    }
+    const uint64_t chunk = pairs <= kBatchSmall ? kPartSub : kBatchChunk;
     const bool small_bins = most * t0->b <= (uint64_t)kMaxFan * kSmallBinSlots;
     const uint64_t R = (small_bins ? kSmallBinSlots : bin_slots<16>()) / t0->b;
     uint64_t n_all = 0, bins = 0, counters = 0;
@@ -2119,7 +2128,7 @@ bht_status bht_batch_create(const bht_batch_entry* entries, uint32_t count, uint
       if (nb > kMaxFan || t->build_mode == BHT_BUILD_CONCURRENT) part = false;
       n_all += entries[i].n_keys;
       bins += nb;
-      counters += ((entries[i].n_keys + kBatchChunk - 1) / kBatchChunk) * nb;
+      counters += ((entries[i].n_keys + chunk - 1) / chunk) * nb;
     }
     if (n_all >= (1ull << 32) || bins >= (1ull << 32)) part = false;
     if (part) {
@@ -2134,8 +2143,8 @@ bht_status bht_batch_create(const bht_batch_entry* entries, uint32_t count, uint
         const uint32_t nb = (uint32_t)((t->m + R - 1) / R);
         parts[i] = {key_off, hist_off, (uint32_t)bin_table.size(), nb};
         uint32_t local = 0;
-        for (uint64_t s0 = 0; s0 < n; s0 += kBatchChunk, ++local)
-          chunks.push_back({i, local, s0, std::min<uint64_t>(kBatchChunk, n - s0)});
+        for (uint64_t s0 = 0; s0 < n; s0 += chunk, ++local)
+          chunks.push_back({i, local, s0, std::min<uint64_t>(chunk, n - s0)});
         for (uint32_t j = 0; j < nb; ++j) bin_table.push_back(i);
         key_off += n;
         hist_off += (uint64_t)local * nb;

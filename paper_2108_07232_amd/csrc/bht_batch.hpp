@@ -124,7 +124,7 @@ __global__ __launch_bounds__(kBlock) void batch_find_kernel(const BatchTable* __
 // Bins of all tables are numbered globally (table t owns bins
 // [bin_off_t, bin_off_t + nbins_t)); placement and overflow insertion run
 // over the global bins.  Work items of the counting and scatter kernels are
-// (table, chunk of at most kBatchChunk pairs); the partitioned pairs live in a
+// (table, chunk of at most 64 K pairs); the partitioned pairs live in a
 // workspace where table t's pairs start at key_off_t.
 
 struct BatchPart {

@@ -73,15 +73,18 @@ constexpr int kPartSub = BHT_PASS_PER * kPassBlock;   // pairs per sub-tile (4-b
 // pairs, 2,048 first-pass chunks; a line-writing pass pads each (chunk,
 // digit) range, so larger chunks pad less: 1.7% and 3.2% of the pairs at
 // 2^28 against 3.4% and 6.3% with 64 K chunks, and the padded first pass
-// fits the slot array up to LF 0.96 at 2^28 pairs, 0.98 at 2^27); the
-// batched build, whose tables are small, cuts chunks of one sub-tile (16 K
-// pairs): at 64 K, 12 M pairs in 256 tables were 371 blocks of one per CU,
-// 83 us for the scatter and 27 for the counts instead of 62 and 17.
+// fits the slot array up to LF 0.96 at 2^28 pairs, 0.98 at 2^27).
 #ifndef BHT_PART_CHUNK_SUBS
 #define BHT_PART_CHUNK_SUBS 8
 #endif
 constexpr uint32_t kPartChunkMax = BHT_PART_CHUNK_SUBS * kPartSub;
-constexpr uint32_t kBatchChunk = kPartSub;
+// Pairs per chunk of the batched build: 64 K, or one sub-tile (16 K) for
+// batches of up to kBatchSmall pairs, which would otherwise be one or two
+// uneven rounds of a block per CU (12 M pairs in 256 tables: 371 chunks, 83 us
+// for the scatter and 27 for the counts instead of 62 and 17).  Larger
+// batches fill the device either way and write longer runs with 64 K.
+constexpr uint32_t kBatchChunk = 4 * kPartSub;
+constexpr uint64_t kBatchSmall = 512ull * kBatchChunk;
 constexpr uint32_t kMaxFan = 1024;                     // digits of the first pass, at most
 constexpr uint32_t kFan2 = 256;                        // digits of the second pass
 constexpr int kLineSub = 8 * kPassBlock;               // pairs per sub-tile of the line-writing scatter
