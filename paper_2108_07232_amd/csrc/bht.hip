@@ -33,6 +33,7 @@ struct bht_table {
   uint64_t m;           // (primary) buckets
   uint32_t key_bits;
   bht_params params;
+  Hash32 hash;          // of params over the m buckets (32-bit keys)
   uint32_t tile;        // lanes per tile reading one bucket
   uint32_t find_schedule;
   uint32_t grid_blocks; // 0 = resident capacity
@@ -253,6 +254,11 @@ Hash32 make_hash32(const bht_params& p, uint64_t m, uint32_t h) {
   H.M = fastmod32_constant((uint32_t)m);
   H.h = h;
   return H;
+}
+
+// After a change of the table's parameters.
+void set_hash(bht_table* t) {
+  if (t->key_bits == 32) t->hash = make_hash32(t->params, t->m, t->params.num_hashes);
 }
 
 // splitmix64 (Steele, Lea, Flood; "Fast splittable pseudorandom number
@@ -1334,6 +1340,7 @@ bht_status create_common(uint64_t capacity_slots, uint32_t bucket_size, bht_sche
   t->m = g.m;
   t->key_bits = params->key_bits;
   t->params = *params;
+  set_hash(t);
   t->tile = default_tile(scheme, bucket_size);
   t->unroll = default_unroll(scheme, bucket_size);
   t->slots = g.slots;
@@ -1406,6 +1413,7 @@ bht_status bht_reseed(bht_table* t, const bht_params* params) {
   if (params->key_bits != t->key_bits || !valid_params(*params, t->scheme, t->b, &why))
     return fail(BHT_ERR_INVALID_ARG, why.empty() ? "key width differs" : why);
   t->params = *params;
+  set_hash(t);
   t->built = false;
   return BHT_OK;
 }
@@ -1680,6 +1688,7 @@ bht_status bht_build_retry(bht_table* t, const void* d_keys, const void* d_value
       bht_params p = t->params;
       draw_constants(seed + attempt - 1, t->key_bits, p.a, p.b, &p.rng_seed);
       t->params = p;
+      set_hash(t);
       t->built = false;
     }
     s = t->key_bits == 64
@@ -2439,7 +2448,7 @@ bht_status bht_multi_find(bht_find_ctx* c, const bht_find_request* reqs, uint32_
       T.out_v = r.d_out_values;
       T.out_f = r.d_out_found;
       T.n = r.n;
-      T.H = make_hash32(r.table->params, r.table->m, r.table->params.num_hashes);
+      T.H = r.table->hash;
       arg.first_item[i] = first;
       first += (uint32_t)((r.n + item_size - 1) / item_size);
     }
