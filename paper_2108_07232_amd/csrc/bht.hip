@@ -75,6 +75,7 @@ struct bht_batch {
   bht::BatchTable* d_tables;
   bht::BatchItem* d_items;      // fill items, then build items, then find items
   uint64_t n_fill, n_build, n_find;
+  uint32_t find_queues;
   unsigned int* d_heads;
   uint32_t* d_status;
   uint32_t* h_status;
@@ -369,6 +370,13 @@ struct KernelSet {
 constexpr uint32_t kDefaultSchedule = BHT_FIND_CHUNK;
 
 constexpr uint64_t kHeadBytes = kQueueHeads * kAtomicLine * 4;  // the heads of one queue
+
+// Queue heads for items of `size` queries: as few as serve the pops (12 ns
+// each on one head), since several drift apart and the tables under way with
+// them (512 tables, 63 M queries, 2,048 per item: 3.39 ms with 16 heads).
+uint32_t find_queue_heads(uint32_t size) {
+  return std::min(std::max(2048u / size, 1u), kQueueHeads);
+}
 
 // Queries per work item of a batch whose caller leaves the size open: about
 // 8 items per resident wave, so that waves do not wait for the last ones, and
@@ -2108,6 +2116,7 @@ bht_status bht_batch_create(const bht_batch_entry* entries, uint32_t count, uint
   b->n_fill = fill.size();
   b->n_build = build.size();
   b->n_find = find.size();
+  b->find_queues = find_queue_heads(find_size);
   for (uint32_t i = 0; i < count; ++i) {
     b->tables.push_back(entries[i].table);
     b->n_keys.push_back(entries[i].n_keys);
@@ -2262,10 +2271,11 @@ bht_status batch_launch(bht_batch* b, hipStream_t st) {
   }
   if (b->n_find) {
     const int grid = grid_for(b->find_kernel, b->n_find * 64);
-    reinterpret_cast<void (*)(const BatchTable*, const BatchItem*, uint32_t, unsigned int*)>(
+    reinterpret_cast<void (*)(const BatchTable*, const BatchItem*, uint32_t, uint32_t, unsigned int*)>(
         const_cast<void*>(b->find_kernel))
         <<<grid, kBlock, 0, st>>>(b->d_tables, b->d_items + b->n_fill + b->n_build,
-                                  (uint32_t)b->n_find, b->d_heads + kHeadBytes / 4);
+                                  (uint32_t)b->n_find, b->find_queues,
+                                  b->d_heads + kHeadBytes / 4);
     HIP_TRY(hipGetLastError());
   }
   return BHT_OK;
@@ -2489,8 +2499,9 @@ bht_status bht_multi_find(bht_find_ctx* c, const bht_find_request* reqs, uint32_
   batch_reset_kernel<<<1, 64, 0, st>>>(c->d_heads, nullptr, 0);
   HIP_TRY(hipGetLastError());
   const int grid = grid_for(fk, k * 64);
-  reinterpret_cast<void (*)(const BatchTable*, const BatchItem*, uint32_t, unsigned int*)>(
-      const_cast<void*>(fk))<<<grid, kBlock, 0, st>>>(c->d_tables, c->d_items, (uint32_t)k, c->d_heads);
+  reinterpret_cast<void (*)(const BatchTable*, const BatchItem*, uint32_t, uint32_t, unsigned int*)>(
+      const_cast<void*>(fk))<<<grid, kBlock, 0, st>>>(c->d_tables, c->d_items, (uint32_t)k,
+                                                        find_queue_heads(item_size), c->d_heads);
   HIP_TRY(hipGetLastError());
   return BHT_OK;
 }

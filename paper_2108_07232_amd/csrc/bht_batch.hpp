@@ -95,7 +95,7 @@ __global__ __launch_bounds__(kBlock) void batch_build_kernel(const BatchTable* _
 template <int B, int W, int Q = 1>
 __global__ __launch_bounds__(kBlock) void batch_find_kernel(const BatchTable* __restrict__ tables,
                                                            const BatchItem* __restrict__ items,
-                                                           uint32_t n_items,
+                                                           uint32_t n_items, uint32_t queues,
                                                            unsigned int* __restrict__ heads) {
   for_items(heads, n_items, [&](uint32_t it) {
     const BatchItem item = items[it];
@@ -112,7 +112,7 @@ __global__ __launch_bounds__(kBlock) void batch_find_kernel(const BatchTable* __
     r.cursor = item.start;
     r.end = item.start + item.count;
     cuckoo_find_chunk_range<B, W, false, Q>(g, r);
-  });
+  }, queues);
 }
 
 // ---------------------------------------------- partitioned batched build

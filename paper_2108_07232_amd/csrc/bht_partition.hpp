@@ -171,11 +171,12 @@ __device__ __forceinline__ void clear_heads(unsigned int* heads, uint32_t i) {
 // block (head q of `queues` hands out the items nwaves + q + queues * i; at
 // most as many heads as blocks, so each is read by some block).
 template <typename F>
-__device__ __forceinline__ void for_items(unsigned int* heads, uint32_t items, F f) {
+__device__ __forceinline__ void for_items(unsigned int* heads, uint32_t items, F f,
+                                          uint32_t most = kQueueHeads) {
   const uint32_t wave =
       __builtin_amdgcn_readfirstlane((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
   const uint32_t nwaves = (gridDim.x * blockDim.x) >> 6;
-  const uint32_t queues = gridDim.x < kQueueHeads ? gridDim.x : kQueueHeads;
+  const uint32_t queues = gridDim.x < most ? gridDim.x : most;
   const uint32_t q = blockIdx.x % queues;
   if (wave < items) f(wave);
   if (items <= nwaves) return;
