@@ -199,10 +199,11 @@ uint64_t bht_build_workspace_bytes(const bht_table* t, uint64_t n);
  * bht_build_workspace_bytes(t, n), 256-byte aligned) instead of allocating
  * one, so a serving loop can keep one workspace per stream and never
  * allocate while building.  The workspace must stay untouched until
- * bht_build_wait returns.  Tables the partitioned path does not apply to
- * (or build_mode = BHT_BUILD_CONCURRENT) are built with the concurrent
- * kernel and the workspace is not used.  INVALID_ARG for a null, too small
- * or misaligned workspace. */
+ * bht_build_wait returns.  Tables for which bht_build_workspace_bytes is 0
+ * (or build_mode = BHT_BUILD_CONCURRENT) are built with a kernel that needs
+ * none and the workspace is not used (two-level iceberg builds of at least
+ * 2^18 pairs use the table's own, as bht_build_async does).  INVALID_ARG for
+ * a null, too small or misaligned workspace. */
 bht_status bht_build_async_in(bht_table* t, const uint32_t* d_keys, const uint32_t* d_values,
                               uint64_t n, void* d_workspace, uint64_t workspace_bytes,
                               void* stream);
@@ -212,8 +213,9 @@ bht_status bht_build_async_in(bht_table* t, const uint32_t* d_keys, const uint32
  * hipMalloc): as bht_build_async_in, but the partitioned path's workspace is
  * a fixed array inside the library (bht_build_noalloc_max_bytes() bytes,
  * about 64 MiB: about 8 M pairs), one per GPU, held until the process ends, so
- * the call allocates nothing.  Builds the default would give the concurrent
- * kernel need no workspace and take that kernel.  Finish with
+ * the call allocates nothing.  Builds below 2^18 pairs (and of tables that
+ * do not take the partitioned path) are made by a kernel that needs no
+ * workspace, and leave the array alone.  Finish with
  * bht_build_wait.  The table's device must be current.  CAPACITY when the
  * build needs more workspace than the array holds.  Every call on one GPU
  * shares that GPU's array: builds through this entry point that overlap on

@@ -991,10 +991,11 @@ bht_status build64_partitioned(bht_table* t, const uint64_t* keys, const uint64_
   return BHT_OK;
 }
 
-// ws: caller-owned workspace of ws_bytes, or null for the table's own.
+// ws: caller-owned workspace of ws_bytes, or null for the table's own, which
+// spare_ws lets grow by the secondary counts (as build32_enqueue's).
 bht_status build32_partitioned(bht_table* t, const uint32_t* keys, const uint32_t* vals,
                                uint64_t n, hipStream_t st, void* ws = nullptr,
-                               uint64_t ws_bytes = 0) {
+                               uint64_t ws_bytes = 0, bool spare_ws = true) {
   PartPlan P;
   if (!part_plan(t, n, &P)) return fail(BHT_ERR_UNSUPPORTED, "table too large to partition");
   PartKernels K;
@@ -1002,7 +1003,7 @@ bht_status build32_partitioned(bht_table* t, const uint32_t* keys, const uint32_
     return fail(BHT_ERR_UNSUPPORTED, "no kernel for this bucket size and tile width");
   PartLayout L = part_layout(P, n);
   // counts of the secondary buckets, in the table's own workspace
-  const bool counted = !ws && iceberg_count_bytes(t, n) != 0;
+  const bool counted = !ws && spare_ws && iceberg_count_bytes(t, n) != 0;
   const uint64_t m2 = t->params.iht_secondary_m;
   const uint64_t counts_at = L.bytes;
   if (counted) L.bytes += iceberg_count_bytes(t, n);
@@ -1131,8 +1132,11 @@ char* table_workspace(bht_table* t, uint64_t bytes, hipStream_t st) {
   return w;
 }
 
+// spare_ws: builds that a kernel without workspace can make as well may take
+// the table's own workspace (allocated or grown as needed); the entry points
+// that promise not to allocate pass false.
 bht_status build32_enqueue(bht_table* t, const uint32_t* keys, const uint32_t* vals, uint64_t n,
-                           unsigned long long* probe_total, void* stream) {
+                           unsigned long long* probe_total, void* stream, bool spare_ws = true) {
   if (!t) return fail(BHT_ERR_INVALID_ARG, "null table");
   if (t->key_bits != 32) return fail(BHT_ERR_INVALID_ARG, "table holds 64-bit keys");
   if (n > t->slots) return fail(BHT_ERR_CAPACITY, "more pairs than slots");
@@ -1146,8 +1150,8 @@ bht_status build32_enqueue(bht_table* t, const uint32_t* keys, const uint32_t* v
   t->counted_build_probes = 0;
   const void* small = n ? small_build(t, probe_total != nullptr) : nullptr;
   if (use_partitioned(t, n, probe_total != nullptr) ||
-      (!small && use_small_partitioned(t, n, probe_total != nullptr, st)))
-    return build32_partitioned(t, keys, vals, n, st);
+      (!small && spare_ws && use_small_partitioned(t, n, probe_total != nullptr, st)))
+    return build32_partitioned(t, keys, vals, n, st, nullptr, 0, spare_ws);
   if (small) {
     ks.build = small;
   } else {
@@ -1163,7 +1167,7 @@ bht_status build32_enqueue(bht_table* t, const uint32_t* keys, const uint32_t* v
     const uint64_t grid_items =
         ks.kind == Kind::Cuckoo ? n : (n + kLbPairsPerLane - 1) / kLbPairsPerLane;
     // the counts take as much memory as the table, at most
-    const void* p2_kernel = p2_count_kernel(t, n, probe_total != nullptr);
+    const void* p2_kernel = spare_ws ? p2_count_kernel(t, n, probe_total != nullptr) : nullptr;
     const uint64_t count_words = t->m * p2_count_stride(t->b);
     uint32_t* counts = p2_kernel
                            ? reinterpret_cast<uint32_t*>(table_workspace(t, count_words * 4, st))
@@ -1448,7 +1452,7 @@ bht_status bht_build_async_in(bht_table* t, const uint32_t* d_keys, const uint32
   if (n && (!d_keys || !d_values)) return fail(BHT_ERR_INVALID_ARG, "null key or value pointer");
   if (!d_workspace) return fail(BHT_ERR_INVALID_ARG, "null workspace");
   if (bht_build_workspace_bytes(t, n) == 0 || t->build_mode == BHT_BUILD_CONCURRENT)
-    return build32_enqueue(t, d_keys, d_values, n, nullptr, stream);    // workspace unused
+    return build32_enqueue(t, d_keys, d_values, n, nullptr, stream, false);    // workspace unused
   KernelSet ks;
   if (!pick(t, t->tile, t->find_schedule, false, &ks))
     return fail(BHT_ERR_UNSUPPORTED, "no kernel for this bucket size and tile width");
@@ -1502,8 +1506,12 @@ bht_status bht_build_async_noalloc(bht_table* t, const uint32_t* d_keys,
   if (t->key_bits != 32) return fail(BHT_ERR_INVALID_ARG, "table holds 64-bit keys");
   if (n > t->slots) return fail(BHT_ERR_CAPACITY, "more pairs than slots");
   if (n && (!d_keys || !d_values)) return fail(BHT_ERR_INVALID_ARG, "null key or value pointer");
-  // the concurrent path has no workspace and allocates nothing
-  if (!use_partitioned(t, n, false)) return build32_enqueue(t, d_keys, d_values, n, nullptr, stream);
+  // Builds below the partitioned path's sizes take a kernel without
+  // workspace, also where bht_build_async would use the table's own: the
+  // fixed array is shared by all builds of the device, and small builds on
+  // several streams need not be kept apart.
+  if (!use_partitioned(t, n, false))
+    return build32_enqueue(t, d_keys, d_values, n, nullptr, stream, false);
   PartPlan P;
   if (!part_plan(t, n, &P)) return fail(BHT_ERR_UNSUPPORTED, "table too large to partition");
   const uint64_t need = part_layout(P, n).bytes;

@@ -88,3 +88,52 @@ def test_noalloc_small_and_oversize():
     dk = dev(keys)
     assert B.bht_build_async_noalloc(t.handle, dk, dk) == B.BHT_ERR_CAPACITY
     t.close()
+
+
+@pytest.mark.parametrize("entry,scheme,b,n", [
+    ("noalloc", "bcht", 16, 1 << 15), ("noalloc", "bcht", 16, 100003),
+    ("noalloc", "bcht", 16, (1 << 18) - 1), ("noalloc", "bcht", 4, 1 << 17),
+    ("noalloc", "cht1", 1, 1 << 17),
+] + [(entry, scheme, 16, n) for entry in ("noalloc", "in") for scheme, n in
+     (("iht", 1 << 10), ("iht", 100003), ("bp2ht", 5000), ("bp2ht", 1 << 20))])
+def test_no_workspace_below_the_partitioned_sizes(entry, scheme, b, n):
+    """Sizes at which bht_build_async takes the table's own workspace: the
+    entry points that promise not to allocate leave free device memory as it
+    is (on a second table, when every kernel is loaded) and build the table
+    all the same."""
+    import torch
+    B = bht()
+    keys, vals = datagen.unique_keys(n, 45), datagen.values(n, 45)
+    dk, dv = dev(keys), dev(vals)
+    ws = torch.empty(1 << 20, dtype=torch.uint8, device="cuda")
+    for attempt in range(12):
+        p = oracle.params_for(scheme, n, 0.75, 4500 + attempt, b=b, max_chain=512)
+        if scheme == "iht":
+            p.b2, p.threshold = 8, b
+            p.m2 = max(1, p.m * b // 64)
+        t = B.Table(p.m * b, b, scheme, p.a, p.c, rng_seed=p.rng_seed, max_chain=512,
+                    iht_threshold=p.threshold if scheme == "iht" else 0, iht_secondary_b=p.b2,
+                    iht_secondary_m=p.m2)
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        if entry == "noalloc":
+            assert B.bht_build_async_noalloc(t.handle, dk, dv) == B.BHT_OK
+        else:
+            B.bht_build_async_in(t.handle, dk, dv, ws)
+        st = B.bht_build_wait(t.handle)
+        after = torch.cuda.mem_get_info()[0]
+        if st == B.BHT_OK and attempt:
+            break
+        t.close()
+    else:
+        pytest.fail("no build succeeded")
+    assert after == before
+    assert not B.bht_build_stats(t.handle)[0]
+    code, msg = oracle.check32(p, t.download(), keys, vals)
+    assert code == 0, msg
+    q = datagen.mixed_queries(n, 2 * n, 0.5, 45)
+    v, f = lookups(t, q)
+    ev, ef = oracle.brute_find32(keys, vals, q)
+    np.testing.assert_array_equal(f, ef)
+    np.testing.assert_array_equal(v, ev)
+    t.close()
