@@ -557,15 +557,28 @@ const void* wave_find(const bht_table* t, uint64_t n, bool count) {
 // 392 and 268, 2^23 615 and 528; past that its two loads and an atomic beside
 // the stored pair leave the last-level cache: 2^24 1288 and 1306, 2^26 5684
 // and 6951.  2^20 pairs with 48, 64, 96, 128, 256 K lanes: 98, 90, 92, 96,
-// 134).
+// 134).  Each choice is made on current counts, but pairs that contend are
+// placed late, so with every pair of a small build under way the order is no
+// longer a random one and builds near their load limit fail: of 500 builds
+// each at ten sizes from 1,000 to 300,007 pairs and load factors the serial
+// order reaches 97% of the time, 4,882 succeeded with the bucket-reading
+// kernel, 4,898 and 4,829 with an eighth and a quarter of the pairs under
+// way; 20,000 pairs in 8-slot buckets at LF 0.72, all under way: 287 of 500
+// against 488.  An eighth costs 36 -> 54 us at 5,000 pairs and nothing from
+// 2^19 on.
 constexpr uint64_t kP2CountMaxKeys = 1ull << 23;
 constexpr uint64_t kP2Lanes = 1ull << 16;
+uint64_t p2_lanes(uint64_t n) { return std::min(std::max<uint64_t>(n / 8, 64), kP2Lanes); }
 
 // The same for the secondary step of two-level iceberg builds (whole build at
 // LF 0.8, us, bucket-reading and counted: 2^18 pairs 144 and 43, 10^6 122 and
 // 68, 3,000,017 123 and 87, 2^23 269 and 240, 2^24 418 and 386, 2^26 1190 and
-// 1249).
+// 1249).  Two lanes per secondary bucket (a quarter of its slots' pairs under
+// way), for the reason above: 100,003 pairs, 32 slots, LF 0.93, builds of 500
+// that succeed: 278 in the concurrent build, 301, 279 and 206 here with 1, 2
+// and 4 lanes per bucket, 27 with every pair under way.
 constexpr uint64_t kIcebergCountMaxKeys = 1ull << 24;
+uint64_t iceberg_count_lanes(uint64_t m2) { return std::min(std::max<uint64_t>(2 * m2, 64), kP2Lanes); }
 
 // Bytes of the counts of n pairs' build (0: secondaries are read).
 uint64_t iceberg_count_bytes(const bht_table* t, uint64_t n) {
@@ -1065,9 +1078,11 @@ bht_status build32_partitioned(bht_table* t, const uint32_t* keys, const uint32_
     const uint64_t sec_buckets = t->params.iht_secondary_b ? t->params.iht_secondary_m : t->m;
     const uint64_t lanes = std::max<uint64_t>(sec_buckets / kIcebergOverflowSpread, 64);
     const void* kernel = counted ? K.overflow_both : K.overflow;
-    int ig = std::min(grid_for(kernel, lanes, t->grid_blocks), 1 << 20);
+    int ig = std::min(grid_for(kernel, lanes, t->grid_blocks), 1 << 20), block = kBlock;
     if (counted) {
-      ig = std::min(grid_for(kernel, kP2Lanes, t->grid_blocks), 1 << 20);
+      const uint64_t count_lanes = iceberg_count_lanes(m2);
+      ig = std::min(grid_for(kernel, count_lanes, t->grid_blocks), 1 << 20);
+      block = (int)std::min<uint64_t>((count_lanes + 63) / 64 * 64, kBlock);
       ia.counts = reinterpret_cast<uint32_t*>(w + counts_at);
       const int clear_grid = (int)std::min<uint64_t>((m2 + kBlock - 1) / kBlock, 4096);
       p2_clear_kernel<<<clear_grid, kBlock, 0, st>>>(ia.counts, m2,
@@ -1075,7 +1090,7 @@ bht_status build32_partitioned(bht_table* t, const uint32_t* keys, const uint32_
     }
     ia.parts = overflow_parts(ig, P.nbins);
     reinterpret_cast<void (*)(IcebergOverflowArgs)>(const_cast<void*>(kernel))
-        <<<ig, kBlock, 0, st>>>(ia);
+        <<<ig, block, 0, st>>>(ia);
   } else {
     OverflowArgs oa;
     oa.g.slots = t->d_slots;
@@ -1188,9 +1203,11 @@ bht_status build32_enqueue(bht_table* t, const uint32_t* keys, const uint32_t* v
       g.n = n;
       g.status = t->d_status;
       g.H = make_hash32(t->params, t->m, t->params.num_hashes);
-      const int cgrid = grid_for(p2_kernel, std::min(n, kP2Lanes), t->grid_blocks);
+      const uint64_t lanes = p2_lanes(n);
+      const int cgrid = grid_for(p2_kernel, lanes, t->grid_blocks);
+      const int cblock = (int)std::min<uint64_t>((lanes + 63) / 64 * 64, kBlock);
       reinterpret_cast<void (*)(P2CountArgs)>(const_cast<void*>(p2_kernel))
-          <<<cgrid, kBlock, 0, st>>>(g);
+          <<<cgrid, cblock, 0, st>>>(g);
     } else if (ks.kind == Kind::Cuckoo || ks.kind == Kind::LoadBalanced) {
       BuildArgs32 g;
       g.slots = t->d_slots;

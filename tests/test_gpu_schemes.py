@@ -419,3 +419,30 @@ def test_iceberg_counted_secondaries(b, thr, lf, n):
     if B.bht_build_wait(t.handle) == B.BHT_OK:
         assert oracle.check32(p, t.download(), keys, vals)[0] == 0
     t.close()
+
+
+@pytest.mark.parametrize("scheme,b,lf,n,seeds", [
+    ("bp2ht", 8, 0.72, 20000, 60), ("bp2ht", 16, 0.86, 20000, 60), ("bp2ht", 16, 0.87, 5000, 60),
+    ("bp2ht", 16, 0.85, 1000, 60), ("iht", 16, 0.88, 100003, 40), ("iht", 32, 0.92, 100003, 40),
+    ("iht", 16, 0.88, 20000, 40), ("iht", 16, 0.9, 2000, 60),
+])
+def test_counted_builds_succeed_as_often_as_serial_ones(scheme, b, lf, n, seeds):
+    """Near the load limit a build's success depends on the order in which the
+    pairs choose.  Over the same keys and constants the library's builds
+    succeed about as often as the serial insertion's: the two counts differ by
+    the order of independent builds, so by less than 4 standard deviations of
+    the difference of two binomials of the serial rate (estimated with one
+    success and one failure added), plus 1."""
+    ours = serial = 0
+    for s in range(seeds):
+        keys, vals = workload(n, 9300 + s)
+        if scheme == "iht":
+            p = iceberg_params(n, lf, 9300 + s, b=b, b2=8, threshold=b)
+        else:
+            p = oracle.params_for(scheme, n, lf, 9300 + s, b=b)
+        serial += oracle.build32(p, keys, vals)[0] == oracle.OK
+        t = gpu_table(p)
+        ours += t.build(dev(keys), dev(vals)) == bht().BHT_OK
+        t.close()
+    rate = (serial + 1) / (seeds + 2)
+    assert ours >= serial - 4 * (2 * seeds * rate * (1 - rate)) ** 0.5 - 1, (ours, serial, seeds)
