@@ -801,6 +801,14 @@ bool use_partitioned(const bht_table* t, uint64_t n, bool counting) {
 
 char* table_workspace(bht_table* t, uint64_t bytes, hipStream_t st);
 
+// Whether work on this stream is being captured (or cannot be told).
+bool capturing(hipStream_t st) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cap) == hipSuccess) return cap != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
+}
+
 // Two-level iceberg builds from this many pairs on (LF 0.8, us, concurrent
 // and partitioned with counted secondaries: 20,000 pairs 239 and 45, 40,000
 // 267 and 35, 100,003 265 and 37, 200,000 273 and 40), where primaries fill
@@ -1016,7 +1024,7 @@ bht_status build32_partitioned(bht_table* t, const uint32_t* keys, const uint32_
     return fail(BHT_ERR_UNSUPPORTED, "no kernel for this bucket size and tile width");
   PartLayout L = part_layout(P, n);
   // counts of the secondary buckets, in the table's own workspace
-  const bool counted = !ws && spare_ws && iceberg_count_bytes(t, n) != 0;
+  const bool counted = !ws && spare_ws && iceberg_count_bytes(t, n) != 0 && !capturing(st);
   const uint64_t m2 = t->params.iht_secondary_m;
   const uint64_t counts_at = L.bytes;
   if (counted) L.bytes += iceberg_count_bytes(t, n);
@@ -1128,18 +1136,13 @@ const void* p2_count_kernel(const bht_table* t, uint64_t n, bool counting) {
 }
 
 // The table's own workspace of at least `bytes`, or null where it is neither
-// at hand nor can be allocated now.
+// at hand nor can be allocated, and always while the stream is captured: a
+// graph would keep its address, and a later, larger build frees it.
 char* table_workspace(bht_table* t, uint64_t bytes, hipStream_t st) {
   PartLayout L{};
   L.bytes = bytes;
   char* w = nullptr;
-  if (t->part_bytes < bytes) {
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
-      (void)hipGetLastError();
-      return nullptr;
-    }
-  }
+  if (capturing(st)) return nullptr;
   if (part_workspace(t, L, st, nullptr, 0, &w) != BHT_OK) {
     (void)hipGetLastError();
     return nullptr;
