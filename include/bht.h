@@ -299,7 +299,8 @@ bht_status bht_get_probe_stats(const bht_table* t, uint64_t* build_probes, uint6
  * layout obeys the same invariants
  * (every key in a candidate bucket, the early-exit property).  It allocates a
  * library-owned workspace of about 8-9 bytes per pair on first use (kept
- * until bht_destroy).  Iceberg tables (Section III-C) take the same path
+ * until bht_destroy, also when a larger one replaces it after a build was
+ * captured with it).  Iceberg tables (Section III-C) take the same path
  * with primaries filled on chip up to iht_threshold pairs and the rest
  * inserted at their secondary choices afterwards, concurrently (a pair
  * reaches the secondary level only once its primary holds iht_threshold

@@ -57,6 +57,8 @@ struct bht_table {
   bool unroll_set;         // ... asked for by the caller
   void* d_part;            // partitioned build workspace (library-owned)
   uint64_t part_bytes;
+  bool part_captured;      // a captured build uses d_part
+  std::vector<void*> kept; // outgrown workspaces that captured builds use
   bool pending_partitioned;
   bool last_partitioned;   // the last successful build took the partitioned path
   uint64_t last_evicted;   // ... and evicted this many pairs on chip
@@ -855,6 +857,8 @@ const void* small_build(const bht_table* t, bool counting) {
 
 // *w <- the workspace for layout L: the caller's ws (of ws_bytes), or, when
 // ws is null, the table's own, allocated on first use and grown as needed.
+// A workspace whose address a capture has taken is kept until the table is
+// destroyed: the graph may be replayed after it was outgrown.
 bht_status part_workspace(bht_table* t, const PartLayout& L, hipStream_t st, void* ws,
                           uint64_t ws_bytes, char** w) {
   if (ws && (ws_bytes < L.bytes || (reinterpret_cast<uintptr_t>(ws) & 255)))
@@ -862,10 +866,15 @@ bht_status part_workspace(bht_table* t, const PartLayout& L, hipStream_t st, voi
   if (!ws && t->part_bytes < L.bytes) {
     // grow the workspace; the stream's earlier work may still use the old one
     if (t->d_part) {
-      HIP_TRY(hipStreamSynchronize(st));
-      HIP_TRY(hipFree(t->d_part));
+      if (t->part_captured) {
+        t->kept.push_back(t->d_part);
+      } else {
+        HIP_TRY(hipStreamSynchronize(st));
+        HIP_TRY(hipFree(t->d_part));
+      }
       t->d_part = nullptr;
       t->part_bytes = 0;
+      t->part_captured = false;
     }
     hipError_t e = hipMalloc(&t->d_part, L.bytes);
     if (e != hipSuccess) {
@@ -874,6 +883,7 @@ bht_status part_workspace(bht_table* t, const PartLayout& L, hipStream_t st, voi
     }
     t->part_bytes = L.bytes;
   }
+  if (!ws && capturing(st)) t->part_captured = true;
   *w = static_cast<char*>(ws ? ws : t->d_part);
   return BHT_OK;
 }
@@ -1436,6 +1446,7 @@ void bht_destroy(bht_table* t) {
     for (int i = 0; i < 4; ++i) (void)hipEventDestroy(t->ev[i]);
   if (t->owns_memory) (void)hipFree(t->d_slots);
   if (t->d_part) (void)hipFree(t->d_part);
+  for (void* w : t->kept) (void)hipFree(w);
   delete t;
 }
 

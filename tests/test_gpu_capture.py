@@ -99,3 +99,32 @@ def test_captured_iceberg_build_asks_for_no_more_than_is_at_hand():
     assert B.bht_build_wait(t.handle) == B.BHT_OK
     check(t, p, keys[:n], vals[:n])
     t.close()
+
+
+def test_captured_workspace_outlives_a_larger_build():
+    """From 2^18 pairs a captured build uses the table's workspace, which
+    stays allocated when a larger build replaces it."""
+    import torch
+    B = bht()
+    n, more = 1 << 18, 1 << 20
+    few, many = workload(n, 64), workload(more, 65)
+    dk, dv, dk2, dv2 = dev(few[0]), dev(few[1]), dev(many[0]), dev(many[1])
+    for last in (False, True):                         # the first time loads the kernels
+        p, t = table_for("bcht", more, 0.8, 6400)
+        assert t.build(dk, dv) == B.BHT_OK
+        graph = capture(t, dk, dv)
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        assert t.build(dk2, dv2) == B.BHT_OK
+        taken = before - torch.cuda.mem_get_info()[0]
+        if not last:
+            t.close()
+    assert taken >= B.bht_build_workspace_bytes(t.handle, more)     # nothing was freed for it
+    check(t, p, *many)
+    for _ in range(2):
+        graph.replay()
+        torch.cuda.synchronize()
+        check(t, p, *few)
+    assert t.build(dk2, dv2) == B.BHT_OK
+    check(t, p, *many)
+    t.close()
