@@ -1344,6 +1344,50 @@ uint64_t bht_hash64(uint64_t a, uint64_t b, uint64_t k, uint64_t m) {
 
 namespace {
 
+// Host memory that kernels write build statuses to: one pinned page of
+// 64-byte slots for the process, allocated with the first table and held
+// until the process ends; a slot is taken for the length of one wait.
+// Coherent, whatever the environment makes of memory without that flag: the
+// host polls a slot while the kernel that writes it is running.
+class StatusSlots {
+ public:
+  // Allocates the page if it is not there yet, so that waits allocate nothing.
+  void reserve() {
+    std::lock_guard<std::mutex> lock(mu_);
+    if (tried_) return;
+    tried_ = true;
+    void* p = nullptr;
+    if (hipHostMalloc(&p, kSlots * 64,
+                      hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) ==
+        hipSuccess) {
+      for (int i = 0; i < kSlots; ++i) free_[n_free_++] = static_cast<uint32_t*>(p) + 16 * i;
+    } else {
+      (void)hipGetLastError();
+    }
+  }
+  // A slot, or null when none is free.
+  uint32_t* take() {
+    std::lock_guard<std::mutex> lock(mu_);
+    return n_free_ ? free_[--n_free_] : nullptr;
+  }
+  void give(uint32_t* s) {
+    std::lock_guard<std::mutex> lock(mu_);
+    free_[n_free_++] = s;
+  }
+
+ private:
+  static constexpr int kSlots = 64;
+  std::mutex mu_;
+  bool tried_ = false;
+  int n_free_ = 0;
+  uint32_t* free_[kSlots];
+};
+
+StatusSlots& status_slots() {
+  static StatusSlots* slots = new StatusSlots();   // outlives every caller
+  return *slots;
+}
+
 // Geometry of a table; returns false (with *why) for invalid parameters.
 struct Geometry {
   uint64_t m, slots, words, slot_bytes, total_bytes;
@@ -1413,6 +1457,7 @@ bht_status create_common(uint64_t capacity_slots, uint32_t bucket_size, bht_sche
     delete t;
     return hip_fail(e, "reading the status area");
   }
+  status_slots().reserve();
   *out = t;
   return BHT_OK;
 }
@@ -1567,44 +1612,6 @@ bht_status bht_build_async_noalloc(bht_table* t, const uint32_t* d_keys,
 }  // extern "C"
 
 namespace {
-
-// Host memory that kernels write build statuses to: one pinned page of
-// 64-byte slots for the process, allocated on first use and held until it
-// ends; a slot is taken for the length of one wait.
-class StatusSlots {
- public:
-  uint32_t* take() {
-    std::lock_guard<std::mutex> lock(mu_);
-    if (!tried_) {
-      tried_ = true;
-      void* p = nullptr;
-      if (hipHostMalloc(&p, kSlots * 64, hipHostMallocPortable) == hipSuccess) {
-        for (int i = 0; i < kSlots; ++i) free_.push_back(static_cast<uint32_t*>(p) + 16 * i);
-      } else {
-        (void)hipGetLastError();
-      }
-    }
-    if (free_.empty()) return nullptr;
-    uint32_t* s = free_.back();
-    free_.pop_back();
-    return s;
-  }
-  void give(uint32_t* s) {
-    std::lock_guard<std::mutex> lock(mu_);
-    free_.push_back(s);
-  }
-
- private:
-  static constexpr int kSlots = 64;
-  std::mutex mu_;
-  bool tried_ = false;
-  std::vector<uint32_t*> free_;
-};
-
-StatusSlots& status_slots() {
-  static StatusSlots* slots = new StatusSlots();   // outlives every caller
-  return *slots;
-}
 
 // Waits for the stream's work on table t and reads the build status into
 // t->h_status.  A one-lane kernel writes the status to a pinned slot that
