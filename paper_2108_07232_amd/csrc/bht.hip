@@ -1620,8 +1620,13 @@ namespace {
 // synchronization (13.5 us with either a pinned copy or this kernel and a
 // synchronization).  Polling gives way to the synchronization, which
 // reports errors, after 2 s.  The copy serves when no slot is free or
-// another device is current.
+// another device is current.  A captured stream is refused before anything
+// is recorded in it: its work does not run until the graph is launched.
 bht_status read_status(bht_table* t, hipStream_t st) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cap) != hipSuccess) (void)hipGetLastError();
+  if (cap != hipStreamCaptureStatusNone)
+    return fail(BHT_ERR_HIP, "cannot wait for a build while its stream is being captured");
   int dev = -1;
   uint32_t* slot = hipGetDevice(&dev) == hipSuccess && dev == t->device ? status_slots().take()
                                                                         : nullptr;
@@ -1643,7 +1648,10 @@ bht_status read_status(bht_table* t, hipStream_t st) {
   uint32_t done = 0;
   for (uint32_t spins = 1; !done; ++spins) {
     done = __atomic_load_n(flag, __ATOMIC_ACQUIRE);
-    if (!done && spins % 4096 == 0 && std::chrono::steady_clock::now() > until) break;
+    if (!done && spins % 1024 == 0 && std::chrono::steady_clock::now() > until) break;
+#if defined(__x86_64__)
+    if (!done) __builtin_ia32_pause();
+#endif
   }
   if (!done) {
     // a slot whose kernel may still run is not given back

@@ -56,3 +56,30 @@ def test_wait_does_not_depend_on_the_environment():
     assert out.returncode == 0, out.stderr
     assert float(out.stdout.split("worst")[1]) < 1.0
     assert builds_and_waits() < 1.0
+
+
+def test_wait_in_a_capture_is_refused_at_once():
+    """Waiting for a build in a stream that is being captured fails without
+    waiting and leaves the capture as it is: the graph builds the table when
+    it is launched."""
+    import torch
+    B = bht()
+    keys, vals = workload(5000, 73)
+    dk, dv = dev(keys), dev(vals)
+    p, t = table_for(5000, 7300)
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        B.bht_build_async(t.handle, dk, dv, stream=side)
+        t0 = time.perf_counter()
+        for _ in range(3):
+            with pytest.raises(B.BhtError) as e:
+                B.bht_build_wait(t.handle, stream=side)
+            assert e.value.status == B.BHT_ERR_HIP
+        took = time.perf_counter() - t0
+    assert took < 0.5
+    for _ in range(2):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert B.bht_build_wait(t.handle) == B.BHT_OK
+        assert oracle.check32(p, t.download(), keys, vals) == (0, "ok")
+    t.close()
