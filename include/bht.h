@@ -340,6 +340,9 @@ typedef struct {
   uint32_t query_unroll;
 } bht_tuning;
 bht_status bht_set_tuning(bht_table* t, const bht_tuning* tuning);
+/* The table's tuning; setting it again changes nothing (query_unroll is 0
+ * while it is left open, since a value set turns the default query kernels
+ * off). */
 bht_status bht_get_tuning(const bht_table* t, bht_tuning* tuning);
 
 /* Profiling: when enabled, HIP events are recorded on the call's stream

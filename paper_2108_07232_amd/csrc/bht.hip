@@ -1934,7 +1934,7 @@ bht_status bht_get_tuning(const bht_table* t, bht_tuning* tuning) {
   tuning->grid_blocks = t->grid_blocks;
   tuning->build_mode = t->build_mode;
   tuning->iht_early_exit = t->iht_early_exit;
-  tuning->query_unroll = t->unroll == 2 ? 2 : 1;
+  tuning->query_unroll = t->unroll_set ? t->unroll : 0;
   return BHT_OK;
 }
 

@@ -459,3 +459,27 @@ def test_find_around_the_wave_kernels_sizes(scheme, b, tile):
         np.testing.assert_array_equal(host_u8(pr[:m]), per[:m])
         assert bool((pr[m:] == 9).all())
     t.close()
+
+
+@pytest.mark.parametrize("b,key_bits", [(16, 32), (8, 32), (8, 64)])
+def test_tuning_written_back_changes_nothing(b, key_bits):
+    """What bht_get_tuning returns, set again, is the same tuning: an open
+    query unroll stays open (a value asked for turns the default query kernels
+    off), and one that was asked for stays asked for."""
+    B = bht()
+    a, c = (datagen.hash_constants64 if key_bits == 64 else datagen.hash_constants)(5, 3)
+    t = B.Table(1000, b, "bcht", a, c, key_bits=key_bits)
+    first = B.bht_get_tuning(t.handle)
+    assert first[5] == 0
+    B.bht_set_tuning(t.handle, *first)
+    assert B.bht_get_tuning(t.handle) == first
+    if key_bits == 32:
+        for unroll in (1, 2):
+            B.bht_set_tuning(t.handle, query_unroll=unroll)
+            asked = B.bht_get_tuning(t.handle)
+            assert asked[5] == unroll
+            B.bht_set_tuning(t.handle, *asked)
+            assert B.bht_get_tuning(t.handle) == asked
+        B.bht_set_tuning(t.handle)
+        assert B.bht_get_tuning(t.handle) == first
+    t.close()
