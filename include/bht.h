@@ -132,7 +132,14 @@ bht_status bht_reseed(bht_table* t, const bht_params* params);
  * Placements that compare bucket loads (BP2HT, IHT secondaries) read the
  * candidates with device-scope loads and, when a concurrent placement takes
  * the chosen slot first, read both again and choose again; those re-reads
- * count as bucket reads in bht_build_counted. */
+ * count as bucket reads in bht_build_counted.  BP2HT builds of up to 2^23
+ * pairs into tables of the library's own memory, and the secondary step of
+ * two-level iceberg builds of up to 2^24, decide from one counter per bucket
+ * instead, which names the slot as well (bht_build_counted always reads the
+ * buckets).  The counters, min(128, 8 bucket_size) bytes per bucket, are kept
+ * with the table until bht_destroy; where they would exceed 64 MiB (48 MiB
+ * for secondaries), or cannot be allocated, or the stream is captured, the
+ * buckets are read. */
 bht_status bht_build(bht_table* t, const uint32_t* d_keys, const uint32_t* d_values,
                      uint64_t n, void* stream);
 

@@ -568,7 +568,15 @@ const void* wave_find(const bht_table* t, uint64_t n, bool count) {
 // way; 20,000 pairs in 8-slot buckets at LF 0.72, all under way: 287 of 500
 // against 488.  An eighth costs 36 -> 54 us at 5,000 pairs and nothing from
 // 2^19 on.
+// At most kP2CountMaxBytes of counters, whatever the number of pairs: with
+// more, a table built once waits longer for their allocation than the kernel
+// saves (16-slot buckets, creation and first build, us, bucket-reading and
+// counted: 63 MB of counters 544 and 523, 72 MB 561 and 617, 96 MB 700 and
+// 805; repeated builds there 514 and 427, 501 and 428, 637 and 563), and a
+// sparse table would pay for clearing them (1,000 pairs in 2^25 slots 95 and
+// 175).
 constexpr uint64_t kP2CountMaxKeys = 1ull << 23;
+constexpr uint64_t kP2CountMaxBytes = 64ull << 20;
 constexpr uint64_t kP2Lanes = 1ull << 16;
 uint64_t p2_lanes(uint64_t n) { return std::min(std::max<uint64_t>(n / 8, 64), kP2Lanes); }
 
@@ -579,13 +587,18 @@ uint64_t p2_lanes(uint64_t n) { return std::min(std::max<uint64_t>(n / 8, 64), k
 // way), for the reason above: 100,003 pairs, 32 slots, LF 0.93, builds of 500
 // that succeed: 278 in the concurrent build, 301, 279 and 206 here with 1, 2
 // and 4 lanes per bucket, 27 with every pair under way.
+// At most kIcebergCountMaxBytes of counters, of which 2^24 pairs at LF 0.75
+// with secondaries of a quarter of the primary use 40 MB (repeated builds 490
+// and 386 us).
 constexpr uint64_t kIcebergCountMaxKeys = 1ull << 24;
+constexpr uint64_t kIcebergCountMaxBytes = 48ull << 20;
 uint64_t iceberg_count_lanes(uint64_t m2) { return std::min(std::max<uint64_t>(2 * m2, 64), kP2Lanes); }
 
 // Bytes of the counts of n pairs' build (0: secondaries are read).
 uint64_t iceberg_count_bytes(const bht_table* t, uint64_t n) {
   if (t->scheme != BHT_IHT || !t->params.iht_secondary_b || n > kIcebergCountMaxKeys) return 0;
-  return t->params.iht_secondary_m * p2_count_stride(t->params.iht_secondary_b) * 4;
+  const uint64_t bytes = t->params.iht_secondary_m * p2_count_stride(t->params.iht_secondary_b) * 4;
+  return bytes <= kIcebergCountMaxBytes ? bytes : 0;
 }
 
 struct PartKernels {
@@ -827,7 +840,7 @@ constexpr uint64_t kIcebergSmallKeys = 1ull << 10;
 bool use_small_partitioned(bht_table* t, uint64_t n, bool counting, hipStream_t st) {
   if (counting || n >= kPartWorkspaceKeys) return false;
   if (t->scheme == BHT_IHT) {
-    if (!t->params.iht_secondary_b || t->params.iht_threshold < t->b || n < kIcebergSmallKeys)
+    if (t->params.iht_threshold < t->b || n < kIcebergSmallKeys || !iceberg_count_bytes(t, n))
       return false;
   } else if ((t->scheme != BHT_BCHT && t->scheme != BHT_CHT1) || n < part_min_keys(t->b)) {
     return false;
@@ -1032,15 +1045,18 @@ bht_status build32_partitioned(bht_table* t, const uint32_t* keys, const uint32_
   PartKernels K;
   if (!part_kernels(t, t->tile, &K))
     return fail(BHT_ERR_UNSUPPORTED, "no kernel for this bucket size and tile width");
-  PartLayout L = part_layout(P, n);
-  // counts of the secondary buckets, in the table's own workspace
-  const bool counted = !ws && spare_ws && iceberg_count_bytes(t, n) != 0 && !capturing(st);
+  const PartLayout L = part_layout(P, n);
+  // counts of the secondary buckets, in the table's own workspace where it
+  // has or can get room for them
   const uint64_t m2 = t->params.iht_secondary_m;
-  const uint64_t counts_at = L.bytes;
-  if (counted) L.bytes += iceberg_count_bytes(t, n);
+  const uint64_t counts_at = L.bytes, count_bytes = iceberg_count_bytes(t, n);
   char* w = nullptr;
-  bht_status ws_status = part_workspace(t, L, st, ws, ws_bytes, &w);
-  if (ws_status != BHT_OK) return ws_status;
+  if (!ws && spare_ws && count_bytes) w = table_workspace(t, L.bytes + count_bytes, st);
+  const bool counted = w != nullptr;
+  if (!counted) {
+    bht_status ws_status = part_workspace(t, L, st, ws, ws_bytes, &w);
+    if (ws_status != BHT_OK) return ws_status;
+  }
   const PartMeta M = part_meta(L, w);
   uint32_t* keys2 = reinterpret_cast<uint32_t*>(w + L.keys);
   uint32_t* vals2 = reinterpret_cast<uint32_t*>(w + L.vals);
@@ -1140,6 +1156,7 @@ bht_status build32_partitioned(bht_table* t, const uint32_t* keys, const uint32_
 // The counted power-of-two build of n pairs into table t, or null.
 const void* p2_count_kernel(const bht_table* t, uint64_t n, bool counting) {
   if (t->scheme != BHT_BP2HT || counting || !t->owns_memory || n > kP2CountMaxKeys) return nullptr;
+  if (t->m * p2_count_stride(t->b) * 4 > kP2CountMaxBytes) return nullptr;
   return t->b == 8    ? (const void*)p2_count_build_kernel<8>
          : t->b == 16 ? (const void*)p2_count_build_kernel<16>
          : t->b == 32 ? (const void*)p2_count_build_kernel<32> : nullptr;
@@ -1194,7 +1211,6 @@ bht_status build32_enqueue(bht_table* t, const uint32_t* keys, const uint32_t* v
     // placement matches the serial rule; large tables still fill the device.
     const uint64_t grid_items =
         ks.kind == Kind::Cuckoo ? n : (n + kLbPairsPerLane - 1) / kLbPairsPerLane;
-    // the counts take as much memory as the table, at most
     const void* p2_kernel = spare_ws ? p2_count_kernel(t, n, probe_total != nullptr) : nullptr;
     const uint64_t count_words = t->m * p2_count_stride(t->b);
     uint32_t* counts = p2_kernel

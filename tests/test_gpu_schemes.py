@@ -446,3 +446,28 @@ def test_counted_builds_succeed_as_often_as_serial_ones(scheme, b, lf, n, seeds)
         t.close()
     rate = (serial + 1) / (seeds + 2)
     assert ours >= serial - 4 * (2 * seeds * rate * (1 - rate)) ** 0.5 - 1, (ours, serial, seeds)
+
+
+@pytest.mark.parametrize("scheme,slots,n", [("bp2ht", 1 << 25, 1000), ("iht", 1 << 27, 2000)])
+def test_sparse_tables_are_built_without_counters(scheme, slots, n):
+    """Few pairs in a large table: counters, as large as the slots they count,
+    would take as much memory and time as the table itself, so the build keeps
+    no memory of that size and reads the buckets."""
+    import torch
+    keys, vals = workload(n, 94)
+    dk, dv = dev(keys), dev(vals)
+    p = oracle.params_for(scheme, n, 0.5, 9400, b=16)
+    p.m = slots // 16
+    if scheme == "iht":
+        p.threshold, p.b2, p.m2 = 16, 8, slots // 64
+    for last in (False, True):                     # the first time loads the kernels
+        t = gpu_table(p)
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        assert t.build(dk, dv) == bht().BHT_OK
+        taken = before - torch.cuda.mem_get_info()[0]
+        if not last:
+            t.close()
+    assert taken < 32 << 20
+    check_find(t, p, keys, vals, datagen.mixed_queries(n, 2 * n, 0.5, 94))
+    t.close()
