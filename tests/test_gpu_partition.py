@@ -414,3 +414,34 @@ def test_overflow_queues_with_a_given_grid(grid):
     assert part and evicted == int(np.maximum(counts - 16, 0).sum())
     assert evicted <= probes < 4 * evicted
     t.close()
+
+
+@pytest.mark.parametrize("scheme,b,n,lf,part", [
+    ("bcht", 16, 40000, 0.51, True), ("bcht", 16, 40000, 0.49, False),
+    ("bcht", 8, 131071, 0.3, False), ("bcht", 8, 1 << 17, 0.3, True),
+    ("bcht", 16, 200003, 0.126, True), ("bcht", 16, 200003, 0.12, False),
+    ("bcht", 4, 140000, 0.01, False), ("cht1", 1, 140000, 0.55, True), ("cht1", 1, 140000, 0.45, False),
+    ("wide", 8, 40000, 0.2, False), ("wide", 8, 200003, 0.3, True), ("wide", 8, 200003, 0.01, False),
+    ("iht", 16, 5000, 0.02, True), ("iht", 16, 5000, 0.002, False),
+])
+def test_sparse_small_builds_are_concurrent(scheme, b, n, lf, part):
+    """Below 2^18 pairs a default build is partitioned only into a table that
+    is loaded enough, on both sides of that load; either way every lookup is
+    right."""
+    import torch
+    B = bht()
+    wide = scheme == "wide"
+    keys = datagen.unique_keys64(n, 86) if wide else datagen.unique_keys(n, 86)
+    vals = datagen.values64(n, 86) if wide else datagen.values(n, 86)
+    p = oracle.params_for("bcht" if wide else scheme, n, lf, 8600, b=b, wide=wide)
+    kw = dict(iht_threshold=16, iht_secondary_b=8, iht_secondary_m=p.m // 4) if scheme == "iht" else {}
+    t = B.Table(p.m * b, b, p.scheme, p.a, p.c, key_bits=64 if wide else 32, rng_seed=p.rng_seed, **kw)
+    assert t.build(dev(keys), dev(vals)) == B.BHT_OK
+    assert B.bht_build_stats(t.handle)[0] == part
+    q = datagen.mixed_queries(n, 2 * n, 0.5, 86, wide=wide)
+    v, f = t.find(dev(q))
+    torch.cuda.synchronize()
+    ev, ef = (oracle.brute_find64 if wide else oracle.brute_find32)(keys, vals, q)
+    np.testing.assert_array_equal(host_u8(f), ef)
+    np.testing.assert_array_equal(v.cpu().numpy().view(ev.dtype), ev)
+    t.close()
