@@ -78,6 +78,7 @@ struct bht_batch {
   bht::BatchItem* d_items;      // fill items, then build items, then find items
   uint64_t n_fill, n_build, n_find;
   uint32_t find_queues;
+  bht::FindCut find_cut;
   unsigned int* d_heads;
   uint32_t* d_status;
   uint32_t* h_status;
@@ -392,6 +393,15 @@ uint32_t find_item_size(const void* kernel, uint64_t queries, uint32_t chunk) {
   const uint64_t even = queries / (waves * 8) / chunk * chunk;
   const uint64_t most = std::min<uint64_t>(std::max<uint64_t>(256, (queries >> 20) / chunk * chunk), 8192);
   return (uint32_t)std::min<uint64_t>(std::max<uint64_t>(even, chunk), most);
+}
+
+// The cut of `tables` tables' `queries` queries into items of `size`: listed
+// ranges of up to 8,192 queries, shorter where tables have few, so that there
+// are no more empty pieces than others.
+FindCut find_cut(uint32_t size, uint64_t queries, uint64_t tables) {
+  uint32_t shift = 0;
+  while ((uint64_t)size << (shift + 1) <= 8192 && tables << (shift + 1) <= queries / size) ++shift;
+  return {size, shift};
 }
 
 template <int B, int W, bool C>
@@ -2163,8 +2173,9 @@ bht_status bht_batch_create(const bht_batch_entry* entries, uint32_t count, uint
   BHT_BATCH_PCASE(32, 16)
 #undef BHT_BATCH_PCASE
 
-  const uint32_t find_size =
-      open_size ? find_item_size(fk, total_q, 64 * unroll) : item_size;
+  const FindCut cut = open_size ? find_cut(find_item_size(fk, total_q, 64 * unroll), total_q, count)
+                                : FindCut{item_size, 0};
+  const uint64_t find_range = (uint64_t)cut.size << cut.shift;
   std::vector<BatchTable> tables(count);
   std::vector<BatchItem> fill, build, find;
   const uint64_t fill_words = 1ull << 16;
@@ -2188,10 +2199,10 @@ bht_status bht_batch_create(const bht_batch_entry* entries, uint32_t count, uint
       fill.push_back({i, 0, s, std::min<uint64_t>(fill_words, t->words - s)});
     for (uint64_t s = 0; s < e.n_keys; s += item_size)
       build.push_back({i, 0, s, std::min<uint64_t>(item_size, e.n_keys - s)});
-    for (uint64_t s = 0; s < e.n_queries; s += find_size)
-      find.push_back({i, 0, s, std::min<uint64_t>(find_size, e.n_queries - s)});
+    for (uint64_t s = 0; s < e.n_queries; s += find_range)
+      find.push_back({i, 0, s, std::min<uint64_t>(find_range, e.n_queries - s)});
   }
-  if (build.size() > 0xFFFFFFFFull || find.size() > 0xFFFFFFFFull)
+  if (build.size() > 0xFFFFFFFFull || find.size() > 0xFFFFFFFFull >> cut.shift)
     return fail(BHT_ERR_CAPACITY, "more than 2^32 - 1 work items");
   bht_batch* b = new bht_batch();
   b->count = count;
@@ -2202,7 +2213,8 @@ bht_status bht_batch_create(const bht_batch_entry* entries, uint32_t count, uint
   b->n_fill = fill.size();
   b->n_build = build.size();
   b->n_find = find.size();
-  b->find_queues = find_queue_heads(find_size);
+  b->find_cut = cut;
+  b->find_queues = find_queue_heads(cut.size);
   for (uint32_t i = 0; i < count; ++i) {
     b->tables.push_back(entries[i].table);
     b->n_keys.push_back(entries[i].n_keys);
@@ -2356,11 +2368,11 @@ bht_status batch_launch(bht_batch* b, hipStream_t st) {
     HIP_TRY(hipGetLastError());
   }
   if (b->n_find) {
-    const int grid = grid_for(b->find_kernel, b->n_find * 64);
-    reinterpret_cast<void (*)(const BatchTable*, const BatchItem*, uint32_t, uint32_t, unsigned int*)>(
-        const_cast<void*>(b->find_kernel))
+    const int grid = grid_for(b->find_kernel, (b->n_find << b->find_cut.shift) * 64);
+    reinterpret_cast<void (*)(const BatchTable*, const BatchItem*, uint32_t, FindCut, uint32_t,
+                              unsigned int*)>(const_cast<void*>(b->find_kernel))
         <<<grid, kBlock, 0, st>>>(b->d_tables, b->d_items + b->n_fill + b->n_build,
-                                  (uint32_t)b->n_find, b->find_queues,
+                                  (uint32_t)b->n_find, b->find_cut, b->find_queues,
                                   b->d_heads + kHeadBytes / 4);
     HIP_TRY(hipGetLastError());
   }
@@ -2585,9 +2597,10 @@ bht_status bht_multi_find(bht_find_ctx* c, const bht_find_request* reqs, uint32_
   batch_reset_kernel<<<1, 64, 0, st>>>(c->d_heads, nullptr, 0);
   HIP_TRY(hipGetLastError());
   const int grid = grid_for(fk, k * 64);
-  reinterpret_cast<void (*)(const BatchTable*, const BatchItem*, uint32_t, uint32_t, unsigned int*)>(
-      const_cast<void*>(fk))<<<grid, kBlock, 0, st>>>(c->d_tables, c->d_items, (uint32_t)k,
-                                                        find_queue_heads(item_size), c->d_heads);
+  reinterpret_cast<void (*)(const BatchTable*, const BatchItem*, uint32_t, FindCut, uint32_t,
+                            unsigned int*)>(const_cast<void*>(fk))
+      <<<grid, kBlock, 0, st>>>(c->d_tables, c->d_items, (uint32_t)k, FindCut{item_size, 0},
+                                find_queue_heads(item_size), c->d_heads);
   HIP_TRY(hipGetLastError());
   return BHT_OK;
 }

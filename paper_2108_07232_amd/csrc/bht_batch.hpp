@@ -92,13 +92,25 @@ __global__ __launch_bounds__(kBlock) void batch_build_kernel(const BatchTable* _
   });
 }
 
+// How the listed ranges of queries are cut into work items: 2^shift pieces
+// of `size` queries each (the last ones of a short range are empty).  The
+// cutting is left to the waves because the list is made and copied on the
+// host when the batch is created: 101 M queries in items of 256 took 5.0 ms
+// to list one by one, 0.5 ms in ranges of 8,192.
+struct FindCut {
+  uint32_t size, shift;
+};
+
 template <int B, int W, int Q = 1>
 __global__ __launch_bounds__(kBlock) void batch_find_kernel(const BatchTable* __restrict__ tables,
                                                            const BatchItem* __restrict__ items,
-                                                           uint32_t n_items, uint32_t queues,
+                                                           uint32_t n_items, FindCut cut,
+                                                           uint32_t queues,
                                                            unsigned int* __restrict__ heads) {
-  for_items(heads, n_items, [&](uint32_t it) {
-    const BatchItem item = items[it];
+  for_items(heads, n_items << cut.shift, [&](uint32_t it) {
+    const BatchItem item = items[it >> cut.shift];
+    const uint64_t skip = (uint64_t)(it & ((1u << cut.shift) - 1)) * cut.size;
+    if (skip >= item.count) return;
     const BatchTable& T = tables[item.table];
     FindArgs32 g;
     g.slots = T.slots;
@@ -109,8 +121,8 @@ __global__ __launch_bounds__(kBlock) void batch_find_kernel(const BatchTable* __
     g.probes = nullptr;
     g.H = T.H;
     Range r;
-    r.cursor = item.start;
-    r.end = item.start + item.count;
+    r.cursor = item.start + skip;
+    r.end = item.start + (item.count - skip < cut.size ? item.count : skip + cut.size);
     cuckoo_find_chunk_range<B, W, false, Q>(g, r);
   }, queues);
 }

@@ -234,3 +234,61 @@ def test_batch_default_item_size(sizes, unroll):
     bht.bht_batch_destroy(batch)
     for d in tabs:
         d["table"].close()
+
+
+@pytest.mark.parametrize("sizes", [
+    [8191, 8192, 8193, 40000],                 # ranges cut short, whole and with one query more
+    [50] * 200 + [300007],                     # short ranges beside a long one
+    [2049] * 64 + [65537, 1, 16385],
+])
+def test_batch_open_items_cut_on_the_device(sizes):
+    """The size of the query items left open: the listed ranges are cut into
+    pieces by the waves, and every query of ragged ranges is answered once,
+    on replays too."""
+    import paper_2108_07232_amd as bht
+    tabs = make_tables(len(sizes), 0, 0, 33, tile=4, sizes=sizes, lf=0.8)
+    entries = [(d["table"].handle, d["dk"], d["dv"], d["dq"], d["ov"], d["of"]) for d in tabs]
+    batch = bht.bht_batch_create(entries)
+    for _ in range(2):
+        for d in tabs:
+            d["ov"].fill_(123)
+            d["of"].fill_(5)
+        bht.bht_batch_run(batch)
+        rc, sts = bht.bht_batch_wait(batch, len(tabs))
+        assert rc == bht.BHT_OK, sts
+        check_outputs(tabs, sts)
+    bht.bht_batch_destroy(batch)
+    for d in tabs:
+        d["table"].close()
+
+
+def test_creating_a_batch_of_many_queries_lists_no_small_items():
+    """A batch is created anew by every bht_batch_build_find, so its host work
+    counts: with the item size left open it lists no more than with items of
+    8,192 queries (2^29 queries in all; the batch is not run)."""
+    import ctypes
+    import time
+    import torch
+    import paper_2108_07232_amd as bht
+    tabs = make_tables(8, 0, 0, 34, tile=4, sizes=[1000] * 8, lf=0.8)
+    arr = bht._batch_entries([(d["table"].handle, d["dk"], d["dv"], d["dq"], d["ov"], d["of"])
+                              for d in tabs])
+    for e in arr:
+        e.n_queries = 1 << 26
+
+    def fastest(item_size):
+        times = []
+        for _ in range(5):
+            torch.cuda.synchronize()
+            out = ctypes.c_void_p()
+            t0 = time.perf_counter()
+            assert bht._lib.bht_batch_create(arr, len(tabs), item_size,
+                                             ctypes.byref(out)) == bht.BHT_OK
+            times.append(time.perf_counter() - t0)
+            bht.bht_batch_destroy(out)
+        return min(times)
+
+    given = fastest(8192)
+    assert fastest(0) <= 3 * given + 1e-3
+    for d in tabs:
+        d["table"].close()
