@@ -164,10 +164,7 @@ int resident_blocks(const void* kernel, int block) {
 // device keeps resident at once (the kernels loop over their share).
 // items_per_lane > 0 asks for at least ceil(items / (256 * items_per_lane))
 // blocks even beyond the resident count: short per-wave ranges let the
-// dispatcher balance waves that finish at different times.  The queries of
-// the 64-bit and the stable schemes take one chunk per wave (us, resident
-// waves or 16 per lane against 1: 2^22 64-bit queries 146 and 132, 3,000,017
-// iceberg 91 and 81.5, 2^20 power-of-two 30 and 26).
+// dispatcher balance waves that finish at different times.
 int grid_for(const void* kernel, uint64_t items, uint32_t fixed = 0, uint64_t items_per_lane = 0) {
   if (fixed) return (int)fixed;
   static std::mutex mu;
@@ -194,6 +191,15 @@ int grid_for(const void* kernel, uint64_t items, uint32_t fixed = 0, uint64_t it
         (items + kBlock * items_per_lane - 1) / (kBlock * items_per_lane), 1u << 20));
   return (int)std::max<uint64_t>(1, grid);
 }
+
+// Queries per lane of the 64-bit and the stable schemes' chunk kernel: a
+// chunk per wave up to 2^22 queries, then more, up to 8, so that launches
+// stay within some 16 K blocks (us at 16, 8, 4, 2, 1 per lane, 16-slot iceberg
+// buckets: 2^20 queries 56, 34, 25, 25, 25; 2^23 on 2^22 pairs 248, 232, 224,
+// 221, 218; 64-bit on 2^16 pairs: 2^24 queries 406, 396, 396, 404, 435; 2^26
+// 1527, 1524, 1558, 1599, 1741: waves over cached tables are short, and their
+// start counts).
+uint64_t chunk_queries(uint64_t n) { return std::min<uint64_t>(std::max<uint64_t>(n >> 22, 1), 8); }
 
 // Work items per bin of an overflow phase over nbins bins run by `blocks`
 // blocks: as many (up to 8) as their waves cover, so that a small build's
@@ -1315,7 +1321,7 @@ bht_status find32_enqueue(const bht_table* t, const uint32_t* q, uint64_t n, uin
   if (wave) ks.find = wave;
   const int grid = wave ? (int)((n + kBlock - 1) / kBlock)
                         : grid_for(ks.find, n, t->grid_blocks,
-                                   !ks.chunk ? 0 : ks.kind == Kind::Cuckoo ? 16 : 1);
+                                   !ks.chunk ? 0 : ks.kind == Kind::Cuckoo ? 16 : chunk_queries(n));
   bht_table* mt = const_cast<bht_table*>(t);
   if (t->timing) HIP_TRY(hipEventRecord(t->ev[2], st));
   if (ks.kind == Kind::Cuckoo) {
@@ -1908,13 +1914,12 @@ bht_status find64_enqueue(const bht_table* t, const uint64_t* q, uint64_t n, uin
   g.probes = probes;
   g.H = make_hash64(t->params, t->m, t->params.num_hashes);
   hipStream_t st = as_stream(stream);
-  // a wave per 64 queries, as wave_find
   const bool lanes = n <= kLaneFindQueries && !t->grid_blocks;
   const void* kernel = lanes ? (probes ? (const void*)wide_find_lane_kernel<true>
                                        : (const void*)wide_find_lane_kernel<false>)
                              : (probes ? (const void*)wide_find_chunk_kernel<8, true>
                                        : (const void*)wide_find_chunk_kernel<8, false>);
-  const int grid = lanes ? (int)((n + kBlock - 1) / kBlock) : grid_for(kernel, n, t->grid_blocks, 1);
+  const int grid = lanes ? (int)((n + kBlock - 1) / kBlock) : grid_for(kernel, n, t->grid_blocks, chunk_queries(n));
   bht_table* mt = const_cast<bht_table*>(t);
   if (t->timing) HIP_TRY(hipEventRecord(t->ev[2], st));
   reinterpret_cast<void (*)(WideFindArgs)>(const_cast<void*>(kernel)) <<<grid, kBlock, 0, st>>>(g);

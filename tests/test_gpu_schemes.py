@@ -471,3 +471,32 @@ def test_sparse_tables_are_built_without_counters(scheme, slots, n):
     assert taken < 32 << 20
     check_find(t, p, keys, vals, datagen.mixed_queries(n, 2 * n, 0.5, 94))
     t.close()
+
+
+@pytest.mark.parametrize("scheme,b", [("bp2ht", 16), ("iht", 32), ("wide", 8)])
+@pytest.mark.parametrize("q", [(1 << 23) - 1, (1 << 23) + 77, (1 << 25) + 65])
+def test_large_query_batches_loop_over_chunks(scheme, b, q):
+    """Query counts around those from which a wave answers two and eight
+    chunks: every query answered, nothing written past the last one."""
+    import torch
+    B = bht()
+    wide, n = scheme == "wide", 3000
+    keys = datagen.unique_keys64(n, 96) if wide else workload(n, 96)[0]
+    vals = datagen.values64(n, 96) if wide else workload(n, 96)[1]
+    p = oracle.params_for("bcht" if wide else scheme, n, 0.6, 9600, b=b, wide=wide)
+    if scheme == "iht":
+        p.threshold = 25
+    t = B.Table(p.m * b, b, p.scheme, p.a, p.c, key_bits=64 if wide else 32, rng_seed=p.rng_seed,
+                iht_threshold=p.threshold)
+    assert t.build(dev(keys), dev(vals)) == B.BHT_OK
+    block = datagen.mixed_queries(n, 4999, 0.5, 96, wide=wide)
+    ev, ef = (oracle.brute_find64 if wide else oracle.brute_find32)(keys, vals, block)
+    turns = -(-q // len(block))
+    dq = dev(block).repeat(turns)[:q].contiguous()
+    ov = torch.full((q + 64,), 7, dtype=dq.dtype, device="cuda")
+    of = torch.full((q + 64,), 7, dtype=torch.uint8, device="cuda")
+    (B.bht_find64 if wide else B.bht_find)(t.handle, dq, ov, of, n=q)
+    assert torch.equal(ov[:q], dev(ev).repeat(turns)[:q])
+    assert torch.equal(of[:q], dev(ef.astype(np.uint8)).repeat(turns)[:q])
+    assert bool((ov[q:] == 7).all()) and bool((of[q:] == 7).all())
+    t.close()
