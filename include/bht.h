@@ -317,8 +317,8 @@ bht_status bht_get_probe_stats(const bht_table* t, uint64_t* build_probes, uint6
  * (iht_threshold = bucket_size), never for one-level ones) into
  * tables whose memory the library owns (bht_create); below 2^18 pairs only
  * where the workspace is allocated or can be, not while the stream is
- * captured, and not into a sparse table (load below 1/2; from 2^17 pairs, with
- * 4 slots per bucket or more, below 1/8; two-level iceberg 1/256).
+ * captured, and not into a sparse table (load below 1/2; from 2^17 pairs below
+ * 1/8; one-slot buckets 0.7, two-level iceberg 1/256).
  * iht_early_exit (iceberg tables only, else UNSUPPORTED): 1 makes a find
  * stop after a miss in a primary bucket that holds fewer than
  * iht_threshold keys, which proves absence because a key goes to a

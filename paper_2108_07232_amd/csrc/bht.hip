@@ -850,19 +850,19 @@ bool capturing(hipStream_t st) {
 // none after all primaries).
 constexpr uint64_t kIcebergSmallKeys = 1ull << 10;
 
-// The least load at which a build below kPartWorkspaceKeys is partitioned,
-// as slots per pair: the path writes every bucket through its bins, and the
+// The least load, in percent, at which a build below kPartWorkspaceKeys is
+// partitioned: the path writes every bucket through its bins, and the
 // concurrent build is at its fastest in a table with room (concurrent and
 // partitioned build, us: 16 slots, 32,768 pairs at LF 0.6 44 and 38, 0.3 35
 // and 35, 0.1 29 and 37, 0.01 27 and 44; 131,072 pairs at LF 0.2 47 and 37,
 // 0.05 38 and 41, 0.01 43 and 105; 8 slots, 65,536 pairs at LF 0.4 37 and 39;
-// one slot, 131,072 pairs at LF 0.8 115 and 103, 0.4 41 and 51; 64-bit pairs,
+// one slot, 131,072 pairs at LF 0.8 115 and 103, 0.6 56 and 63; 64-bit pairs,
 // 131,072 at LF 0.1 49 and 46, 0.05 44 and 49).  Two-level iceberg tables
 // gain until far below (20,000 pairs at LF 0.005 140 and 47; 1,024 at 0.001 36
 // and 38, at 0.0002 39 and 51).
-uint64_t part_max_slots_per_pair(const bht_table* t, uint64_t n) {
-  if (t->scheme == BHT_IHT) return 256;
-  return t->b == 1 || n < (1ull << 17) ? 2 : 8;
+double part_min_load(const bht_table* t, uint64_t n) {
+  if (t->scheme == BHT_IHT) return 100.0 / 256;
+  return t->b == 1 ? 70.0 : n < (1ull << 17) ? 50.0 : 12.5;
 }
 
 // Whether a build below kPartWorkspaceKeys takes the partitioned path
@@ -877,7 +877,7 @@ bool use_small_partitioned(bht_table* t, uint64_t n, bool counting, hipStream_t 
     return false;
   }
   if (t->build_mode != BHT_BUILD_AUTO || !t->owns_memory) return false;
-  if (t->slots > n * part_max_slots_per_pair(t, n)) return false;
+  if (100.0 * (double)n < part_min_load(t, n) * (double)t->slots) return false;
   PartPlan P;
   if (!part_plan(t, n, &P)) return false;
   return table_workspace(t, part_layout(P, n, t->key_bits / 8).bytes + iceberg_count_bytes(t, n),

@@ -53,9 +53,9 @@ def test_captured_small_build_keeps_no_workspace(scheme, n):
     import torch
     B = bht()
     b = 1 if scheme == "cht1" else 16
-    many, few = workload(3 * n // 2, 61), workload(n, 62)
+    many, few = workload(9 * n // 8, 61), workload(n, 62)
     dk, dv = dev(few[0]), dev(few[1])
-    p, t = table_for(scheme, 3 * n // 2, 0.8, 6100, b=b)
+    p, t = table_for(scheme, 9 * n // 8, 0.82, 6100, b=b)
     assert t.build(dk, dv) == B.BHT_OK                 # the workspace is at hand
     graph = capture(t, dk, dv)
     for _ in range(2):

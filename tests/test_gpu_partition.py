@@ -420,7 +420,7 @@ def test_overflow_queues_with_a_given_grid(grid):
     ("bcht", 16, 40000, 0.51, True), ("bcht", 16, 40000, 0.49, False),
     ("bcht", 8, 131071, 0.3, False), ("bcht", 8, 1 << 17, 0.3, True),
     ("bcht", 16, 200003, 0.126, True), ("bcht", 16, 200003, 0.12, False),
-    ("bcht", 4, 140000, 0.01, False), ("cht1", 1, 140000, 0.55, True), ("cht1", 1, 140000, 0.45, False),
+    ("bcht", 4, 140000, 0.01, False), ("cht1", 1, 140000, 0.72, True), ("cht1", 1, 140000, 0.66, False),
     ("wide", 8, 40000, 0.2, False), ("wide", 8, 200003, 0.3, True), ("wide", 8, 200003, 0.01, False),
     ("iht", 16, 5000, 0.02, True), ("iht", 16, 5000, 0.002, False),
 ])
