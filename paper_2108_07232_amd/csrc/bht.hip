@@ -1248,14 +1248,13 @@ bht_status build32_enqueue(bht_table* t, const uint32_t* keys, const uint32_t* v
     uint32_t* counts = p2_kernel
                            ? reinterpret_cast<uint32_t*>(table_workspace(t, count_words * 4, st))
                            : nullptr;
+    const int grid = small ? 1 : grid_for(ks.build, grid_items, t->grid_blocks);
+    const int block = small ? kSmallBlock : kBlock;
+    // clearing the counts is part of the insertion, as in a partitioned build
+    if (t->timing) HIP_TRY(hipEventRecord(t->ev[0], st));
     if (counts) {
       const int clear_grid = (int)std::min<uint64_t>((t->m + kBlock - 1) / kBlock, 4096);
       p2_clear_kernel<<<clear_grid, kBlock, 0, st>>>(counts, t->m, p2_count_stride(t->b));
-    }
-    const int grid = small ? 1 : grid_for(ks.build, grid_items, t->grid_blocks);
-    const int block = small ? kSmallBlock : kBlock;
-    if (t->timing) HIP_TRY(hipEventRecord(t->ev[0], st));
-    if (counts) {
       P2CountArgs g;
       g.slots = t->d_slots;
       g.counts = counts;

@@ -500,3 +500,40 @@ def test_large_query_batches_loop_over_chunks(scheme, b, q):
     assert torch.equal(of[:q], dev(ef.astype(np.uint8)).repeat(turns)[:q])
     assert bool((ov[q:] == 7).all()) and bool((of[q:] == 7).all())
     t.close()
+
+
+def test_counted_build_time_holds_the_clearing_of_its_counters():
+    """bht_kernel_ms of a counted power-of-two build, for few pairs in a table
+    whose counters take far longer to clear: what the whole enqueued build
+    takes beyond the reset of the slots (a build of no pairs) is nearly all in
+    it.  Medians of 25."""
+    import torch
+    B = bht()
+    keys, vals = workload(64, 98)
+    dk, dv = dev(keys), dev(vals)
+    p = oracle.params_for("bp2ht", 64, 0.5, 9800, b=8)
+    p.m = 1 << 20                                  # 64 MiB of slots and of counters
+    t = gpu_table(p)
+    B.bht_enable_timing(t.handle)
+    e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+
+    def timed(n):
+        whole, kernel = [], []
+        for _ in range(25):
+            torch.cuda.synchronize()
+            e0.record()
+            B.bht_build_async(t.handle, dk, dv, n=n)
+            e1.record()
+            assert B.bht_build_wait(t.handle) == B.BHT_OK
+            torch.cuda.synchronize()
+            whole.append(e0.elapsed_time(e1))
+            if n:
+                kernel.append(B.bht_kernel_ms(t.handle)[0])
+        return np.median(whole), np.median(kernel) if n else 0.0
+
+    timed(64)
+    reset, _ = timed(0)
+    whole, kernel = timed(64)
+    print("whole %.4f ms, reset %.4f ms, kernel_ms %.4f" % (whole, reset, kernel))
+    assert kernel >= 0.7 * (whole - reset)
+    t.close()
