@@ -2206,8 +2206,8 @@ bht_status bht_batch_create(const bht_batch_entry* entries, uint32_t count, uint
     for (uint64_t s = 0; s < e.n_queries; s += find_range)
       find.push_back({i, 0, s, std::min<uint64_t>(find_range, e.n_queries - s)});
   }
-  if (build.size() > 0xFFFFFFFFull || find.size() > 0xFFFFFFFFull >> cut.shift)
-    return fail(BHT_ERR_CAPACITY, "more than 2^32 - 1 work items");
+  if (build.size() > kMaxItems || find.size() > kMaxItems >> cut.shift)
+    return fail(BHT_ERR_CAPACITY, "too many work items");
   bht_batch* b = new bht_batch();
   b->count = count;
   b->b = t0->b;
@@ -2516,7 +2516,7 @@ bht_status bht_multi_find(bht_find_ctx* c, const bht_find_request* reqs, uint32_
       return fail(BHT_ERR_INVALID_ARG, "null data pointer in request");
     items += (r.n + item_size - 1) / item_size;
   }
-  if (items > c->max_items || items > 0xFFFFFFFFull)
+  if (items > c->max_items || items > kMaxItems)
     return fail(BHT_ERR_CAPACITY, "more work items than the context holds");
   const void* fk = nullptr;
   const void* ik = nullptr;

@@ -165,6 +165,16 @@ __device__ __forceinline__ void clear_heads(unsigned int* heads, uint32_t i) {
   if (i < kQueueHeads) heads[i * kAtomicLine] = 0;
 }
 
+// Work items of one launch, at most.  Every wave takes one number past the
+// last item before it ends, so the numbers handed out by the heads reach the
+// items, the waves that start with one and a number per wave and head: below
+// 2^32, where they would start again, for grids of up to kMaxQueueWaves.
+constexpr uint32_t kMaxQueueWaves = 1u << 22;
+constexpr uint32_t kMaxItems = 0xFF000000u;
+static_assert((uint64_t)kMaxItems + kMaxQueueWaves + (kMaxQueueWaves + 1ull) + 2 * kQueueHeads <=
+                  0xFFFFFFFFull,
+              "item numbers wrap");
+
 // Calls f(item) in every wave of the grid for its share of `items` work
 // items: each wave starts with the item of its own number and, when there
 // are more items than waves, takes the following ones from the head of its
