@@ -402,11 +402,12 @@ uint32_t find_item_size(const void* kernel, uint64_t queries, uint32_t chunk) {
 }
 
 // The cut of `tables` tables' `queries` queries into items of `size`: listed
-// ranges of up to 8,192 queries, shorter where tables have few, so that there
-// are no more empty pieces than others.
+// ranges of up to 8,192 queries, shorter where tables have few, so that at
+// most an eighth as many pieces are empty as there are others (256 tables, 12
+// M queries, whole run: 455 us with as many, 451 so, 450 listed one by one).
 FindCut find_cut(uint32_t size, uint64_t queries, uint64_t tables) {
   uint32_t shift = 0;
-  while ((uint64_t)size << (shift + 1) <= 8192 && tables << (shift + 1) <= queries / size) ++shift;
+  while ((uint64_t)size << (shift + 1) <= 8192 && tables << (shift + 1) <= queries / size / 8) ++shift;
   return {size, shift};
 }
 
