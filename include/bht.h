@@ -144,8 +144,9 @@ bht_status bht_build(bht_table* t, const uint32_t* d_keys, const uint32_t* d_val
                      uint64_t n, void* stream);
 
 /* As bht_build but only enqueues the work; bht_build_wait then waits for
- * the stream and returns the build's status.  Lets callers time or overlap
- * the build. */
+ * the stream's work so far and returns the build's status.  Lets callers time
+ * or overlap the build.  While the stream is being captured bht_build_wait
+ * returns BHT_ERR_HIP at once and leaves the capture as it is. */
 bht_status bht_build_async(bht_table* t, const uint32_t* d_keys, const uint32_t* d_values,
                            uint64_t n, void* stream);
 bht_status bht_build_wait(bht_table* t, void* stream);
@@ -180,7 +181,8 @@ bht_status bht_build_retry(bht_table* t, const void* d_keys, const void* d_value
  * resident on chip (iceberg tables: pairs that met a primary holding t
  * pairs and went on to the secondary step), and *overflow_probes = bucket
  * reads made while those pairs were inserted (Section VII-E's probe: one
- * bucket read); both 0 for a concurrent build.  Returns NOT_BUILT before a
+ * bucket read; where secondary buckets have counters, two per pair); both 0
+ * for a concurrent build.  Returns NOT_BUILT before a
  * successful build. */
 bht_status bht_build_stats(const bht_table* t, uint32_t* partitioned, uint64_t* evicted,
                            uint64_t* overflow_probes);
@@ -282,7 +284,9 @@ bht_status bht_get_probe_stats(const bht_table* t, uint64_t* build_probes, uint6
 /* Tuning (speed only, never results).  tile_width: lanes that read one
  * bucket together (1 for bucket_size 1; 4, 8 or 16 otherwise, at most
  * bucket_size; 0 keeps the default: 4 for BCHT and CHT1 tables of 16-slot
- * buckets, one 16-byte load per lane for the rest).  find_schedule: BHT_FIND_DEFAULT
+ * buckets, one 16-byte load per lane for the rest; default lookups of up to
+ * 2^17 queries, alone or coalesced, read every bucket with a single lane
+ * whatever the width).  find_schedule: BHT_FIND_DEFAULT
  * (cuckoo tables: a wave per 64 queries, unless a query_unroll or grid_blocks
  * is set; else as BHT_FIND_CHUNK),
  * BHT_FIND_REFILL (a lane that finishes a query takes the next one) or
@@ -405,7 +409,8 @@ bht_status bht_diag_stream(const void* d_src, void* d_dst, uint64_t bytes, uint6
  * their output arrays (all caller-owned device memory, as for bht_build and
  * bht_find).  bht_batch_create copies the table descriptors and the work
  * items (ranges of item_size pairs or queries; 0 = 8192 pairs, and queries
- * as many as spread over the device, 64 to 8192) to the device.
+ * as many as spread over the device, 64 to 256 up to 2^28 queries in all; the
+ * waves cut listed ranges of up to 8192) to the device.
  * bht_batch_run enqueues a reset of the batch's queues and statuses, the
  * build of every table and one persistent query kernel pulling (table,
  * range) items from a device-side queue.  The build is the partitioned

@@ -1,7 +1,7 @@
 // Batched mode: many independent cuckoo tables of uneven sizes built and
 // then queried by persistent kernels that pull (table, range) work items
-// from device-side queues (one atomic counter per phase).  Each wave takes
-// an item, runs the same per-lane insertion or query loop as the
+// from device-side queues (a wave's first item is its own, further ones come
+// from up to 16 counters on separate lines).  Each wave takes an item, runs the same per-lane insertion or query loop as the
 // single-table kernels on that table's range, and takes the next item, so
 // thousands of small tables cost a few launches instead of thousands, and
 // large tables still spread over the whole device.
@@ -131,12 +131,13 @@ __global__ __launch_bounds__(kBlock) void batch_find_kernel(const BatchTable* __
 //
 // The partitioned build of bht_partition.hpp for all tables of a batch at
 // once, with one radix pass per table: a table's pairs are grouped by the
-// bin (8,192 slots) of their first bucket within that table, so pairs of
+// bin (8,192 slots; 2,048 where that leaves no table more than 1,024 bins) of
+// their first bucket within that table, so pairs of
 // different tables never mix and every table needs at most 1,024 bins.
 // Bins of all tables are numbered globally (table t owns bins
 // [bin_off_t, bin_off_t + nbins_t)); placement and overflow insertion run
 // over the global bins.  Work items of the counting and scatter kernels are
-// (table, chunk of at most 64 K pairs); the partitioned pairs live in a
+// (table, chunk of at most 64 K pairs, 16 K in smaller batches); the partitioned pairs live in a
 // workspace where table t's pairs start at key_off_t.
 
 struct BatchPart {

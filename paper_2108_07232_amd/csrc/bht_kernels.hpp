@@ -440,9 +440,9 @@ __device__ __forceinline__ uint32_t cuckoo_build_range(const BuildArgs32& g, Ran
   return flags;
 }
 
-// Where a key evicted from bucket `left` (first: from its first bucket) goes on: `at` is the next bucket of
-// the cuckoo rule (as next_bucket), `alt` the hash after it when there is one
-// (has_alt).  `full`: the key left the bucket of its last hash, so `at` is
+// Where a key evicted from bucket `left` (first: from its first bucket) goes
+// on: `at` is the next bucket of the cuckoo rule (as next_bucket), `alt` the
+// hash after it when there is one (has_alt).  `full`: the key left the bucket of its last hash, so `at` is
 // its first one, which is known to be full (the key was evicted from it
 // before, and buckets never lose pairs).
 struct Choices {
@@ -500,10 +500,15 @@ __device__ __forceinline__ uint32_t lane_load(const uint64_t* bucket) {
 // order, that has room; with both full it is exchanged at the first of them
 // (Section III-A), and the resident goes on the same way.  Looking at the
 // second bucket before evicting keeps the early-exit property (a pair sits
-// past a bucket only if that one is full) and the number of buckets a pair
-// sits beyond its first on average, but at LF 0.9 a chain goes on with
+// past a bucket only if that one is full), but at LF 0.9 a chain goes on with
 // probability 0.22 instead of 0.47 per step, so a launch makes fewer slot
-// atomics and its slowest chain is half as long.
+// atomics and its slowest chain is half as long.  The layouts differ: a stored
+// key is found after 1.093 reads instead of 1.109 on average (2^22 pairs, LF
+// 0.9), but 1.8% of the keys sit in their third bucket instead of 0.3%, so a
+// wave of 64 such queries needs a third round more often.  Where that latency
+// counts, with few waves that each answer many queries, lookups of stored keys
+// take 3 to 5% longer (chunk schedule, 2^18 queries on 2^24 pairs 13.9 -> 14.6
+// us; 48 coalesced requests of 1,000 queries 65 -> 72 us).
 // Every lane reads its own bucket: a small launch has few pairs per wave
 // left after the first steps and is bound by the instructions of the waves'
 // rounds, and 8 loads and 32 compares per bucket take a quarter of the
@@ -823,8 +828,9 @@ __global__ __launch_bounds__(kBlock) void cuckoo_find_wave_kernel(FindArgs32 g) 
 // Same query for launches that leave the device idle, where the length of
 // one wave's instruction stream counts: every lane reads its own bucket
 // whole (8 loads and 48 compares for 16 slots, a third of the instructions
-// of the tile read and match).  256 queries 6.3 us against 7.2 (8.5 with two
-// per lane), 2^17 8.1 against 8.7; from 2^18 the tile read is faster, since
+// of the tile read and match).  Events around the launch: 256 queries 6.3 us
+// against 7.2 (8.5 with two per lane), 2^17 8.1 against 8.7 (kernel alone, 300
+// queries on 2^20 pairs: 6.3 with two per lane, 3.6 here); from 2^18 the tile read is faster, since
 // a lane's loads take the L1 64 cycles each (2^22 on 2^20 pairs: 105 us).
 template <int B, bool COUNT>
 __device__ __forceinline__ void cuckoo_find_lane(const FindArgs32& g, uint64_t idx) {

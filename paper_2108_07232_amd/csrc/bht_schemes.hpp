@@ -222,7 +222,8 @@ __global__ void p2_clear_kernel(uint32_t* __restrict__ counts, uint64_t m, uint3
 // stores itself there.  A count that has changed comes back from the failed
 // compare-and-swap and the pair chooses again.  Counts only grow, so the
 // bucket taken holds no more pairs than the other one at that moment, as in
-// the serial insertion, however many pairs are under way.
+// the serial insertion.  How many pairs are under way still matters for the
+// order: contended pairs are placed late (see p2_lanes in bht.hip).
 // The insertion above reads two 128-byte buckets with 8-byte device-scope
 // loads (eight requests and about 700 instructions a round) and keeps one
 // lane per 32 pairs under way; here a placement is two 4-byte loads, one
