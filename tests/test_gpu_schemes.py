@@ -537,3 +537,29 @@ def test_counted_build_time_holds_the_clearing_of_its_counters():
     print("whole %.4f ms, reset %.4f ms, kernel_ms %.4f" % (whole, reset, kernel))
     assert kernel >= 0.7 * (whole - reset)
     t.close()
+
+
+def test_partitioned_one_level_builds_succeed_as_with_few_waves():
+    """The secondary step of a partitioned one-level iceberg build near its
+    load limit, over 300 constant sets: about as many builds succeed with the
+    device's waves as with 16 blocks, which keep few pairs under way (less than
+    4 standard deviations of the difference of two binomials apart)."""
+    B = bht()
+    n, sets = 1 << 21, 300
+    keys, vals = workload(n, 99)
+    dk, dv = dev(keys), dev(vals)
+    p = oracle.params_for("iht", n, 0.85, 9900, b=16)
+    p.threshold = 13
+    ok = {}
+    for grid in (16, 0):
+        t = B.Table(p.m * 16, 16, "iht", p.a, p.c, rng_seed=p.rng_seed, iht_threshold=13,
+                    build_mode="partitioned", grid_blocks=grid)
+        ok[grid] = 0
+        for s in range(sets):
+            a, c = datagen.hash_constants(9900 + s, 3)
+            B.bht_reseed(t.handle, B.make_params(a, c, rng_seed=datagen.rng_seed(9900 + s),
+                                                 iht_threshold=13))
+            ok[grid] += t.build(dk, dv) == B.BHT_OK
+        t.close()
+    rate = (ok[16] + 1) / (sets + 2)
+    assert ok[0] >= ok[16] - 4 * (2 * sets * rate * (1 - rate)) ** 0.5 - 1, ok
