@@ -4,6 +4,7 @@
 
 #include <algorithm>
 #include <chrono>
+#include <cmath>
 #include <cstdio>
 #include <cstring>
 #include <map>
@@ -584,7 +585,9 @@ const void* wave_find(const bht_table* t, uint64_t n, bool count) {
 // kernel, 4,898 and 4,829 with an eighth and a quarter of the pairs under
 // way; 20,000 pairs in 8-slot buckets at LF 0.72, all under way: 287 of 500
 // against 488.  An eighth costs 36 -> 54 us at 5,000 pairs and nothing from
-// 2^19 on.
+// 2^19 on, so it is kept to loads past p2_free_load (percent), up to which one
+// of 45,000 builds of 64 to 65,536 pairs failed with all under way (four of
+// 21,000 with the bucket-reading kernel).
 // At most kP2CountMaxBytes of counters, whatever the number of pairs: with
 // more, a table built once waits longer for their allocation than the kernel
 // saves (16-slot buckets, creation and first build, us, bucket-reading and
@@ -595,7 +598,11 @@ const void* wave_find(const bht_table* t, uint64_t n, bool count) {
 constexpr uint64_t kP2CountMaxKeys = 1ull << 23;
 constexpr uint64_t kP2CountMaxBytes = 64ull << 20;
 constexpr uint64_t kP2Lanes = 1ull << 16;
-uint64_t p2_lanes(uint64_t n) { return std::min(std::max<uint64_t>(n / 8, 64), kP2Lanes); }
+uint64_t p2_free_load(uint32_t b) { return b == 8 ? 57 : b == 16 ? 80 : 88; }
+uint64_t p2_lanes(const bht_table* t, uint64_t n) {
+  const bool free = 100 * n <= t->slots * p2_free_load(t->b);
+  return std::min(free ? n : std::max<uint64_t>(n / 8, 64), kP2Lanes);
+}
 
 // The same for the secondary step of two-level iceberg builds (whole build at
 // LF 0.8, us, bucket-reading and counted: 2^18 pairs 144 and 43, 10^6 122 and
@@ -603,13 +610,25 @@ uint64_t p2_lanes(uint64_t n) { return std::min(std::max<uint64_t>(n / 8, 64), k
 // 1249).  Two lanes per secondary bucket (a quarter of its slots' pairs under
 // way), for the reason above: 100,003 pairs, 32 slots, LF 0.93, builds of 500
 // that succeed: 278 in the concurrent build, 301, 279 and 206 here with 1, 2
-// and 4 lanes per bucket, 27 with every pair under way.
+// and 4 lanes per bucket, 27 with every pair under way.  Not where the
+// secondaries are expected to stay within the load that a power-of-two table
+// of such buckets reaches with every pair under way (100,003 pairs, LF 0.8:
+// 44 us instead of 55).
 // At most kIcebergCountMaxBytes of counters, of which 2^24 pairs at LF 0.75
 // with secondaries of a quarter of the primary use 40 MB (repeated builds 490
 // and 386 us).
 constexpr uint64_t kIcebergCountMaxKeys = 1ull << 24;
 constexpr uint64_t kIcebergCountMaxBytes = 48ull << 20;
-uint64_t iceberg_count_lanes(uint64_t m2) { return std::min(std::max<uint64_t>(2 * m2, 64), kP2Lanes); }
+uint64_t iceberg_count_lanes(const bht_table* t, uint64_t n) {
+  // pairs past the threshold of a primary that n pairs reach at random
+  const double per = (double)n / (double)t->m;
+  const uint32_t thr = std::min(t->params.iht_threshold, t->b);
+  double over = per - thr, p = std::exp(-per);
+  for (uint32_t k = 0; k < thr; ++k, p *= per / k) over += (thr - k) * p;
+  const uint64_t m2 = t->params.iht_secondary_m, b2 = t->params.iht_secondary_b;
+  if (100.0 * over * (double)t->m <= (double)(p2_free_load((uint32_t)b2) * m2 * b2)) return kP2Lanes;
+  return std::min(std::max<uint64_t>(2 * m2, 64), kP2Lanes);
+}
 
 // Bytes of the counts of n pairs' build (0: secondaries are read).
 uint64_t iceberg_count_bytes(const bht_table* t, uint64_t n) {
@@ -1151,7 +1170,7 @@ bht_status build32_partitioned(bht_table* t, const uint32_t* keys, const uint32_
     ia.parts = 1;
     int ig = std::min(grid_for(kernel, lanes, t->grid_blocks), 1 << 20), block = kBlock;
     if (counted) {
-      const uint64_t count_lanes = iceberg_count_lanes(m2);
+      const uint64_t count_lanes = iceberg_count_lanes(t, n);
       ig = std::min(grid_for(kernel, count_lanes, t->grid_blocks), 1 << 20);
       block = (int)std::min<uint64_t>((count_lanes + 63) / 64 * 64, kBlock);
       ia.counts = reinterpret_cast<uint32_t*>(w + counts_at);
@@ -1268,7 +1287,7 @@ bht_status build32_enqueue(bht_table* t, const uint32_t* keys, const uint32_t* v
       g.n = n;
       g.status = t->d_status;
       g.H = make_hash32(t->params, t->m, t->params.num_hashes);
-      const uint64_t lanes = p2_lanes(n);
+      const uint64_t lanes = p2_lanes(t, n);
       const int cgrid = grid_for(p2_kernel, lanes, t->grid_blocks);
       const int cblock = (int)std::min<uint64_t>((lanes + 63) / 64 * 64, kBlock);
       reinterpret_cast<void (*)(P2CountArgs)>(const_cast<void*>(p2_kernel))

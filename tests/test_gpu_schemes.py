@@ -425,6 +425,9 @@ def test_iceberg_counted_secondaries(b, thr, lf, n):
     ("bp2ht", 8, 0.72, 20000, 60), ("bp2ht", 16, 0.86, 20000, 60), ("bp2ht", 16, 0.87, 5000, 60),
     ("bp2ht", 16, 0.85, 1000, 60), ("iht", 16, 0.88, 100003, 40), ("iht", 32, 0.92, 100003, 40),
     ("iht", 16, 0.88, 20000, 40), ("iht", 16, 0.9, 2000, 60),
+    # the largest loads with every pair under way
+    ("bp2ht", 8, 0.57, 60000, 60), ("bp2ht", 16, 0.8, 60000, 60), ("bp2ht", 32, 0.88, 60000, 40),
+    ("iht", 16, 0.83, 100003, 40), ("iht", 32, 0.89, 100003, 40),
 ])
 def test_counted_builds_succeed_as_often_as_serial_ones(scheme, b, lf, n, seeds):
     """Near the load limit a build's success depends on the order in which the
