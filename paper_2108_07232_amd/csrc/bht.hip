@@ -538,6 +538,8 @@ constexpr uint64_t kPartWorkspaceKeys = 1ull << 18;
 #define BHT_ICEBERG_PART_MIN_LOG2 18
 #endif
 constexpr uint64_t kIcebergPartMinKeys = 1ull << BHT_ICEBERG_PART_MIN_LOG2;
+static_assert(kIcebergPartMinKeys >= kPartWorkspaceKeys,
+              "smaller builds take a workspace only where table_workspace allows it");
 
 // The default query kernel of a cuckoo table for n queries: one wave per 64
 // of them, reading per lane while they leave the device idle.  Null when the
@@ -923,9 +925,10 @@ const void* small_build(const bht_table* t, bool counting) {
 // *w <- the workspace for layout L: the caller's ws (of ws_bytes), or, when
 // ws is null, the table's own, allocated on first use and grown as needed.
 // A workspace whose address a capture has taken is kept until the table is
-// destroyed: the graph may be replayed after it was outgrown.
+// destroyed: the graph may be replayed after it was outgrown.  eager: the
+// stream is known not to be captured.
 bht_status part_workspace(bht_table* t, const PartLayout& L, hipStream_t st, void* ws,
-                          uint64_t ws_bytes, char** w) {
+                          uint64_t ws_bytes, char** w, bool eager = false) {
   if (ws && (ws_bytes < L.bytes || (reinterpret_cast<uintptr_t>(ws) & 255)))
     return fail(BHT_ERR_INVALID_ARG, "workspace too small or not 256-byte aligned");
   if (!ws && t->part_bytes < L.bytes) {
@@ -948,7 +951,7 @@ bht_status part_workspace(bht_table* t, const PartLayout& L, hipStream_t st, voi
     }
     t->part_bytes = L.bytes;
   }
-  if (!ws && capturing(st)) t->part_captured = true;
+  if (!ws && !eager && capturing(st)) t->part_captured = true;
   *w = static_cast<char*>(ws ? ws : t->d_part);
   return BHT_OK;
 }
@@ -1106,7 +1109,9 @@ bht_status build32_partitioned(bht_table* t, const uint32_t* keys, const uint32_
   if (!ws && spare_ws && count_bytes) w = table_workspace(t, L.bytes + count_bytes, st);
   const bool counted = w != nullptr;
   if (!counted) {
-    bht_status ws_status = part_workspace(t, L, st, ws, ws_bytes, &w);
+    // below kPartWorkspaceKeys a default build has found its stream eager
+    const bool eager = !ws && t->build_mode == BHT_BUILD_AUTO && n < kPartWorkspaceKeys;
+    bht_status ws_status = part_workspace(t, L, st, ws, ws_bytes, &w, eager);
     if (ws_status != BHT_OK) return ws_status;
   }
   const PartMeta M = part_meta(L, w);
@@ -1226,7 +1231,7 @@ char* table_workspace(bht_table* t, uint64_t bytes, hipStream_t st) {
   L.bytes = bytes;
   char* w = nullptr;
   if (capturing(st)) return nullptr;
-  if (part_workspace(t, L, st, nullptr, 0, &w) != BHT_OK) {
+  if (part_workspace(t, L, st, nullptr, 0, &w, true) != BHT_OK) {
     (void)hipGetLastError();
     return nullptr;
   }
