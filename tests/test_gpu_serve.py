@@ -116,3 +116,29 @@ def test_few_requests_around_the_per_lane_size(sizes):
     torch.cuda.synchronize()
     bht.bht_find_ctx_destroy(ctx)
     t.close()
+
+
+def test_more_requests_than_fit_the_kernel_arguments_with_a_large_one():
+    """A default coalesced launch past the number of requests that go as kernel
+    arguments, small ones beside one of many work items: each equals the same
+    lookup made alone."""
+    import torch
+    import paper_2108_07232_amd as bht
+    n = 30000
+    keys, vals = datagen.unique_keys(n, 97), datagen.values(n, 97)
+    p = oracle.params_for("bcht", n, 0.85, 97)
+    t = bht.Table(p.m * p.b, p.b, "bcht", p.a, p.c, rng_seed=p.rng_seed)
+    assert t.build(dev(keys), dev(vals)) == bht.BHT_OK
+    sizes = [1, 63, 64, 65, 1000] * 6 + [300007, 8193]
+    ctx = bht.bht_find_ctx_create(64, 4096)
+    q = [dev(datagen.mixed_queries(n, m, 0.5, 200 + i)) for i, m in enumerate(sizes)]
+    outs = [(torch.full((m,), 3, dtype=torch.int32, device="cuda"),
+             torch.full((m,), 3, dtype=torch.uint8, device="cuda")) for m in sizes]
+    for _ in range(2):
+        bht.bht_multi_find(ctx, [(t.handle, a, o[0], o[1]) for a, o in zip(q, outs)])
+    for a, o in zip(q, outs):
+        v, f = t.find(a)
+        assert torch.equal(v, o[0]) and torch.equal(f, o[1])
+    torch.cuda.synchronize()
+    bht.bht_find_ctx_destroy(ctx)
+    t.close()
